@@ -34,12 +34,10 @@
  *    order, so results are reproducible bit for bit across runs and launch shapes.
  *  - Inputs must be finite and non-negative: times, powers, energies (-0.0 counts as 0).
  *    The entry points that take cost tables or point sets accept an optional device
- *    status word (status_out, NULL to skip): when given, a check pass reads every input
- *    value first and the word receives KR_OK, or KR_ENONFINITE if some value is NaN,
- *    infinite or negative (the check reads the inputs once more, so callers that
- *    validated them already pass NULL).  kr_compose_frontiers always checks its points
- *    while it reads them.  With invalid inputs the other outputs are unspecified but
- *    memory-safe.
+ *    status word (status_out, NULL to skip): when given, every input value is checked
+ *    where the kernels read it and the word receives KR_OK, or KR_ENONFINITE if some
+ *    value is NaN, infinite or negative.  kr_compose_frontiers always checks its points.
+ *    With invalid inputs the other outputs are unspecified but memory-safe.
  */
 #ifndef KAREUS_H
 #define KAREUS_H

@@ -193,17 +193,6 @@ bool eval_plan(const kr_space *s, bool fused, EvalArgs *a)
     return true;
 }
 
-// The input check of the cost tables, when the caller asks for a status word.
-hipError_t check_tables(const kr_space *s, const double *t, const double *pw, const double *tc,
-                        const double *pc, int32_t *status, hipStream_t st)
-{
-    const int64_t slabs = (int64_t)s->n_parts * s->n_freq;
-    const int64_t nt = slabs * s->n_kernels * (s->n_sm + 1), nc = slabs * s->n_comm * s->n_sm;
-    const double *xs[4] = {t, pw, tc, pc};
-    const int64_t n[4] = {nt, nt, nc, nc};
-    return launch_check(xs, n, 4, status, st);
-}
-
 // Caller-owned events recorded around a phase (kr_set_phase_events), one setting per
 // host thread: a call reads only its own thread's entries, so threads never race on them.
 thread_local hipEvent_t g_phase_ev[6][2] = {};
@@ -277,8 +266,7 @@ kr_status kr_evaluate_partition(const kr_space *space, const double *t, const do
     a.pc = pc;
     a.T_out = T_out;
     a.E_out = E_out;
-    if (status_out && check_tables(space, t, pw, tc, pc, status_out, (hipStream_t)stream) != hipSuccess)
-        return KR_EHIP;
+    a.status = status_out;
     return launch_eval(a, (hipStream_t)stream) == hipSuccess ? KR_OK : KR_EHIP;
 }
 
@@ -302,11 +290,6 @@ kr_status kr_pareto_filter(int64_t n_total, const double *T, const double *E,
     if (ws_bytes < kr_pareto_filter_workspace(n_total, n_seg)) return KR_ECAPACITY;
     hipStream_t st = (hipStream_t)stream;
     const int64_t n_units = (n_total + KR_TILE - 1) / KR_TILE + n_seg;
-    if (status_out) {
-        const double *xs[2] = {T, E};
-        const int64_t n[2] = {n_total, n_total};
-        if (launch_check(xs, n, 2, status_out, st) != hipSuccess) return KR_EHIP;
-    }
     Carve c(ws);
     FilterWs w = carve_filter(c, n_total, n_seg, n_units, false);
     SegLayout L;
@@ -314,11 +297,13 @@ kr_status kr_pareto_filter(int64_t n_total, const double *T, const double *E,
     L.unit_base = w.unit_base;
     L.n_seg = n_seg;
     L.unit_stride = KR_TILE;
-    if (n_seg > 0 &&
-        launch_tile_layout(seg_off, w.unit_base, n_seg, KR_TILE, w.lists, st) != hipSuccess)
+    if ((n_seg > 0 || status_out) &&
+        launch_tile_layout(seg_off, w.unit_base, n_seg, KR_TILE, w.lists, status_out, st) !=
+            hipSuccess)
         return KR_EHIP;
     UnitOut o{w.buf[0].T, w.buf[0].E, w.buf[0].I, w.ucnt};
-    if (n_seg > 0 && launch_pareto_tiles(T, E, L, n_units, o, st) != hipSuccess) return KR_EHIP;
+    if (n_seg > 0 && launch_pareto_tiles(T, E, L, n_units, o, status_out, st) != hipSuccess)
+        return KR_EHIP;
     return finish_segments(L, w, cap, out_off, out_idx, out_T, out_E, st);
 }
 
@@ -350,14 +335,13 @@ kr_status kr_evaluate_and_filter(const kr_space *space, const double *t, const d
     a.pc = pc;
     Carve c(ws);
     FilterWs w = carve_filter(c, (int64_t)a.P * a.useg, a.P, (int64_t)a.P * a.uper, true);
-    if (launch_uniform_layout(w.seg_off, w.unit_base, a.P, a.useg, a.uper, w.lists, st) !=
-        hipSuccess)
+    a.status = status_out;
+    if (launch_uniform_layout(w.seg_off, w.unit_base, a.P, a.useg, a.uper, w.lists, status_out,
+                              st) != hipSuccess)
         return KR_EHIP;
     UnitOut o{w.buf[0].T, w.buf[0].E, w.buf[0].I, w.ucnt};
     a.dma16 = (a.wave || a.pair) && (a.N * (a.S + 1)) % 2 == 0 && (uintptr_t)t % 16 == 0 &&
               (uintptr_t)pw % 16 == 0;
-    if (status_out && check_tables(space, t, pw, tc, pc, status_out, st) != hipSuccess)
-        return KR_EHIP;
     phase_mark(KR_PHASE_EVAL_TILE, 0, st);
     const hipError_t le = a.wave   ? launch_eval_filter_wave(a, o, st)
                           : a.pair ? launch_eval_filter_pair(a, o, st)

@@ -272,7 +272,13 @@ __global__ void __launch_bounds__(KR_BLOCK) eval_kernel(EvalArgs a)
     const int p = blockIdx.x / a.F, f = blockIdx.x % a.F;
     const size_t pf = (size_t)p * a.F + f;
     const int staged = 2 * a.N * (a.S + 1) + 2 * a.M * a.S;
-    for (int x = threadIdx.x; x < staged; x += KR_BLOCK) lds[x] = slab_elem(a, pf, x);
+    uint32_t worst = 0;
+    for (int x = threadIdx.x; x < staged; x += KR_BLOCK) {
+        const double v = slab_elem(a, pf, x);
+        worst = max(worst, value_hi(v));
+        lds[x] = v;
+    }
+    if (a.status) report_values(a.status, worst >= KR_BAD_HI);
     const Slab L = slab_view(a, lds);
     build_pairs(a, (int32_t *)L.pairs);
     __syncthreads();
@@ -287,8 +293,11 @@ __global__ void __launch_bounds__(KR_BLOCK) eval_kernel(EvalArgs a)
     }
 }
 
+__global__ void status_init_kernel(int32_t *status) { *status = KR_OK; }
+
 hipError_t launch_eval(const EvalArgs &a, hipStream_t st)
 {
+    if (a.status) hipLaunchKernelGGL(status_init_kernel, dim3(1), dim3(1), 0, st, a.status);
     const size_t lds = (size_t)a.lds_doubles * sizeof(double);
     hipLaunchKernelGGL(eval_kernel, dim3(a.P * a.F), dim3(KR_BLOCK), lds, st, a);
     return hipGetLastError();
@@ -323,19 +332,22 @@ struct Prefetch {
         }
     }
 
-    __device__ __forceinline__ void store(const EvalArgs &a, double *lds) const
+    // `worst`: the largest high word stored so far (input check)
+    __device__ __forceinline__ void store(const EvalArgs &a, double *lds, uint32_t &worst) const
     {
         const int slab = a.N * (a.S + 1), ms = a.M * a.S;
 #pragma unroll
         for (int k = 0; k < PFT; ++k) {
             const int x = threadIdx.x + k * KR_BLOCK;
             if (x < slab) {
+                worst = max(worst, max(value_hi(t[k]), value_hi(pw[k])));
                 lds[x] = t[k];
                 lds[slab + x] = pw[k];
             }
         }
         const int x = threadIdx.x;
         if (x < ms) {
+            worst = max(worst, max(value_hi(c[0]), value_hi(c[1])));
             lds[2 * slab + x] = c[0];
             lds[2 * slab + ms + x] = c[1];
         }
@@ -363,12 +375,13 @@ __global__ void __launch_bounds__(KR_BLOCK) eval_filter_kernel(EvalArgs a, UnitO
     double *oT = o.T + slot0, *oE = o.E + slot0;
     int32_t *oI = o.I + slot0;
     int count = 0, parity = 0;
+    uint32_t worst = 0;
     // position runs of the one-comm mapping: thread = (SM choice s, run of cpt positions)
     const int s_of = threadIdx.x % a.S, run = threadIdx.x / a.S;
 
     for (int f = f0; f < f1; ++f) {
         lds_barrier();  // the previous slab is no longer read
-        pre.store(a, lds);
+        pre.store(a, lds, worst);
         if (f + 1 < f1) pre.load(a, (size_t)p * a.F + f + 1);
         lds_barrier();
         running_sums(a, lds);
@@ -416,6 +429,7 @@ __global__ void __launch_bounds__(KR_BLOCK) eval_filter_kernel(EvalArgs a, UnitO
                                         oI + count);
         }
     }
+    if (a.status) report_values(a.status, worst >= KR_BAD_HI);
     if (threadIdx.x == 0) o.cnt[blockIdx.x] = count;
 }
 

@@ -275,6 +275,7 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
     double *const oT = o.T + slot0, *const oE = o.E + slot0;
     int32_t *const oI = o.I + slot0;
     int count = 0;
+    uint32_t worst = 0;  // largest high word read (input check)
     const double p_static = a.p_static;
     // sort room of the slab-end reduction: this wave's share of the fresh and continuing
     // tables
@@ -292,7 +293,9 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
         copy_to_lds_nw<W, NW>(a.pw + pf * slab, Lp, slab);
         const double *const cm = a.tc + pf * 2 * S, *const cpw = a.pc + pf * 2 * S;
         const double tc1 = cm[s1], tc2 = cm[S + s2], tcF = cm[S + sF];
-        const double ct1 = cpw[s1] * tc1, ct2 = cpw[S + s2] * tc2;
+        const double pc1 = cpw[s1], pc2 = cpw[S + s2];
+        const double ct1 = pc1 * tc1, ct2 = pc2 * tc2;
+        worst = max(worst, max(max(value_hi(tc1), value_hi(tc2)), max(value_hi(pc1), value_hi(pc2))));
         __builtin_amdgcn_s_waitcnt(KR_WAIT_VM0);  // this wave's part of slab f is in LDS
         __syncthreads();                          // and the other waves' parts
 
@@ -300,6 +303,7 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
         // ahead of the additions).
         if (tid < S1) {
             double sa = 0.0, sb = 0.0;
+            const uint32_t seen = worst;  // of what came before this column
             AB[tid] = ColRec{0.0, 0.0};
             for (int i0 = 0; i0 < N; i0 += 8) {
                 double vt[8], vw[8];
@@ -312,10 +316,17 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
 #pragma unroll
                 for (int q = 0; q < 8; ++q)
                     if (i0 + q < N) {
+                        worst = max(worst, max(raw_hi(vt[q]), raw_hi(vw[q])));
                         sa = sa + vt[q];
                         sb = sb + vw[q] * vt[q];
                         AB[(i0 + q + 1) * S1 + tid] = ColRec{sa, sb};
                     }
+            }
+            // raw words also stop at -0.0: such a column is looked at again
+            if (worst >= KR_BAD_HI) {
+                worst = seen;
+                for (int i = 0; i < N; ++i)
+                    worst = max(worst, max(value_hi(Lt[i * S1 + tid]), value_hi(Lp[i * S1 + tid])));
             }
         }
         __syncthreads();
@@ -409,6 +420,7 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
         }
         __syncthreads();  // the sort room is free again, and Lt, Lp may be overwritten
     }
+    if (a.status) report_values(a.status, worst >= KR_BAD_HI);
     if (lane == 0) o.cnt[unit] = count;
 }
 

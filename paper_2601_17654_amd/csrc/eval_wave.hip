@@ -136,8 +136,9 @@ __global__ void __launch_bounds__(64) eval_filter_wave_kernel(EvalArgs a, UnitOu
     for (int f = f0; f < f1; ++f) {
         __builtin_amdgcn_s_waitcnt(KR_WAIT_VM0);  // slab f is in LDS
         wave_lds_fence();
-        const double tcm = tc_next;
-        const double ctail = pc_next * tc_next;
+        const double tcm = tc_next, pc_cur = pc_next;
+        const double ctail = pc_cur * tcm;
+        uint32_t worst = max(raw_hi(tcm), raw_hi(pc_cur));  // input check
 
         // Running sums, 8 rows at a time: every lane sums its column (lane 0 the all-SM
         // column, writing the records; the others their comm-time column) and keeps the
@@ -165,6 +166,7 @@ __global__ void __launch_bounds__(64) eval_filter_wave_kernel(EvalArgs a, UnitOu
                 }
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
+                    worst = max(worst, max(raw_hi(vt[q]), raw_hi(vw[q])));
                     ra[q] = sa;
                     rb[q] = sb;
                     sa = sa + vt[q];  // rows past N add +0: exact
@@ -192,6 +194,19 @@ __global__ void __launch_bounds__(64) eval_filter_wave_kernel(EvalArgs a, UnitOu
             b0 = bitsd(lane_u64(dbits(sb), 0));
         }
         wave_lds_fence();
+        // Input check: the sums read every value of the slab (each lane its column, lane 0
+        // the all-SM one; with 64 SM choices no lane is left for column 1).  A raw high
+        // word at KR_BAD_HI or above is a bad value or -0.0: the slab is looked at again.
+        // The one maximum per row cost nothing that could be measured.
+        if (SC == 0 && S == 64)
+            for (int i = lane; i < N; i += 64)
+                worst = max(worst, max(raw_hi(Lt[i * S1 + 1]), raw_hi(Lp[i * S1 + 1])));
+        if (a.status && __ballot(worst >= KR_BAD_HI)) {
+            worst = max(value_hi(tcm), value_hi(pc_cur));
+            for (int x = lane; x < slab; x += 64)
+                worst = max(worst, max(value_hi(Lt[x]), value_hi(Lp[x])));
+            report_values(a.status, worst >= KR_BAD_HI);
+        }
 
         int j = plo;  // end cursor
         double jA = pA, jB = pB;

@@ -20,6 +20,7 @@ namespace kr {
 struct EvalArgs {
     const double *t, *pw, *tc, *pc;
     double *T_out, *E_out;  // unfused evaluation only
+    int32_t *status;        // input check's verdict (KR_OK before the launch), or NULL
     int P, N, M, F, S, n_pos, n_pp;
     int Cf;                 // candidates per frequency
     int64_t C;              // candidates per partition
@@ -83,6 +84,8 @@ struct PointBufs {
     int32_t *I;
 };
 
+// Writes KR_OK to a.status first when there is one; the other evaluation launches expect
+// it there (launch_uniform_layout).
 hipError_t launch_eval(const EvalArgs &a, hipStream_t st);
 hipError_t launch_eval_filter(const EvalArgs &a, const UnitOut &o, hipStream_t st);
 hipError_t launch_eval_filter_wave(const EvalArgs &a, const UnitOut &o, hipStream_t st);
@@ -92,14 +95,17 @@ int pair_owner_host(int p1, int NW);
 hipError_t launch_decode(const DecodeArgs &d, hipStream_t st);
 
 // pareto.hip
-// Both layouts also clear lists[0], which launch_finalize expects to be zero.
+// Both layouts also clear lists[0], which launch_finalize expects to be zero, and write
+// KR_OK to *status when it is not NULL.
 hipError_t launch_uniform_layout(int64_t *seg_off, int64_t *unit_base, int n_seg,
                                  int64_t seg_len, int64_t units_per_seg, int32_t *lists,
-                                 hipStream_t st);
+                                 int32_t *status, hipStream_t st);
 hipError_t launch_tile_layout(const int64_t *seg_off, int64_t *unit_base, int n_seg, int tile,
-                              int32_t *lists, hipStream_t st);
+                              int32_t *lists, int32_t *status, hipStream_t st);
+// status: NULL, or the input check's verdict
 hipError_t launch_pareto_tiles(const double *T, const double *E, const SegLayout &L,
-                               int64_t n_units_bound, const UnitOut &o, hipStream_t st);
+                               int64_t n_units_bound, const UnitOut &o, int32_t *status,
+                               hipStream_t st);
 // lists: 2 * n_seg + 2 ints of scratch, lists[0] zero on entry (cleared by the layout
 // launches above)
 hipError_t launch_finalize(const SegLayout &L, const PointBufs &buf, const int32_t *ucnt,
@@ -139,11 +145,6 @@ struct ComposeArgs {
     int32_t *L_out, *stair_bin, *n_stair, *status;
     double *stair_Tlo, *stair_E;
 };
-// check.hip: status = KR_ENONFINITE if some value of the arrays is NaN, infinite or
-// negative (-0.0 counts as 0), else KR_OK.
-hipError_t launch_check(const double *const *xs, const int64_t *n, int count, int32_t *status,
-                        hipStream_t st);
-
 hipError_t launch_compose(const ComposeArgs &a, const ComposeWs &w, hipEvent_t *minplus_ev,
                           hipStream_t st);
 

@@ -20,12 +20,15 @@
 namespace kr {
 
 // The layout kernels also clear lists[0], the count of segments that the first merge
-// stage passes on (so that the merge needs no launch of its own for it).
+// stage passes on, and the input check's verdict (so that neither needs a launch of its
+// own).
 __global__ void uniform_layout_kernel(int64_t *seg_off, int64_t *unit_base, int n_seg,
-                                      int64_t seg_len, int64_t units_per_seg, int32_t *lists)
+                                      int64_t seg_len, int64_t units_per_seg, int32_t *lists,
+                                      int32_t *status)
 {
     const int g = blockIdx.x * KR_BLOCK + threadIdx.x;
     if (g == 0) lists[0] = 0;
+    if (g == 0 && status) *status = KR_OK;
     if (g > n_seg) return;
     seg_off[g] = (int64_t)g * seg_len;
     unit_base[g] = (int64_t)g * units_per_seg;
@@ -33,21 +36,22 @@ __global__ void uniform_layout_kernel(int64_t *seg_off, int64_t *unit_base, int 
 
 hipError_t launch_uniform_layout(int64_t *seg_off, int64_t *unit_base, int n_seg,
                                  int64_t seg_len, int64_t units_per_seg, int32_t *lists,
-                                 hipStream_t st)
+                                 int32_t *status, hipStream_t st)
 {
     hipLaunchKernelGGL(uniform_layout_kernel, dim3((n_seg + 1 + KR_BLOCK - 1) / KR_BLOCK),
                        dim3(KR_BLOCK), 0, st, seg_off, unit_base, n_seg, seg_len, units_per_seg,
-                       lists);
+                       lists, status);
     return hipGetLastError();
 }
 
 // unit_base = exclusive prefix sum of ceil(len_g / tile); one block.
 __global__ void __launch_bounds__(KR_BLOCK)
 tile_layout_kernel(const int64_t *seg_off, int64_t *unit_base, int n_seg, int tile,
-                   int32_t *lists)
+                   int32_t *lists, int32_t *status)
 {
     __shared__ int64_t sc[KR_WAVES];
     if (threadIdx.x == 0) lists[0] = 0;
+    if (threadIdx.x == 0 && status) *status = KR_OK;
     int64_t carry = 0;
     for (int g0 = 0; g0 < n_seg; g0 += KR_BLOCK) {
         const int g = g0 + threadIdx.x;
@@ -65,10 +69,10 @@ tile_layout_kernel(const int64_t *seg_off, int64_t *unit_base, int n_seg, int ti
 }
 
 hipError_t launch_tile_layout(const int64_t *seg_off, int64_t *unit_base, int n_seg, int tile,
-                              int32_t *lists, hipStream_t st)
+                              int32_t *lists, int32_t *status, hipStream_t st)
 {
     hipLaunchKernelGGL(tile_layout_kernel, dim3(1), dim3(KR_BLOCK), 0, st, seg_off, unit_base,
-                       n_seg, tile, lists);
+                       n_seg, tile, lists, status);
     return hipGetLastError();
 }
 
@@ -90,7 +94,7 @@ __device__ __forceinline__ int find_segment(const int64_t *unit_base, int n_seg,
 // their survivors.
 template <bool BIG>
 __global__ void __launch_bounds__(KR_BLOCK)
-pareto_tile_kernel(const double *T, const double *E, SegLayout L, UnitOut o)
+pareto_tile_kernel(const double *T, const double *E, SegLayout L, UnitOut o, int32_t *status)
 {
     static_assert(KR_TILE == 8 * KR_BLOCK, "a tile is 8 points per thread");
     extern __shared__ double tile_lds[];
@@ -127,6 +131,12 @@ pareto_tile_kernel(const double *T, const double *E, SegLayout L, UnitOut o)
         vE[q] = ok[q] ? E[x] + 0.0 : 0.0;
         vI[q] = (int32_t)(x - s0);
     }
+    if (!BIG && status) {  // every point is in one tile, and the first pass reads them all
+        uint32_t worst = 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) worst = max(worst, max(raw_hi(vT[q]), raw_hi(vE[q])));
+        report_values(status, worst >= KR_BAD_HI);
+    }
     int parity = 0;
     const int n = tile_frontier<8>(vT, vE, vI, ok, fl, parity, o.T + start, o.E + start,
                                    o.I + start);
@@ -134,14 +144,15 @@ pareto_tile_kernel(const double *T, const double *E, SegLayout L, UnitOut o)
 }
 
 hipError_t launch_pareto_tiles(const double *T, const double *E, const SegLayout &L,
-                               int64_t n_units_bound, const UnitOut &o, hipStream_t st)
+                               int64_t n_units_bound, const UnitOut &o, int32_t *status,
+                               hipStream_t st)
 {
     if (n_units_bound == 0) return hipSuccess;
     const size_t lds = (size_t)KR_SURV_CAP * 20, lds_big = (size_t)KR_TILE * 20;
     hipLaunchKernelGGL(pareto_tile_kernel<false>, dim3((unsigned)n_units_bound), dim3(KR_BLOCK),
-                       lds, st, T, E, L, o);
+                       lds, st, T, E, L, o, status);
     hipLaunchKernelGGL(pareto_tile_kernel<true>, dim3((unsigned)n_units_bound), dim3(KR_BLOCK),
-                       lds_big, st, T, E, L, o);
+                       lds_big, st, T, E, L, o, status);
     return hipGetLastError();
 }
 
