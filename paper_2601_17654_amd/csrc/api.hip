@@ -48,6 +48,24 @@ int64_t cand_per_freq(const kr_space *s)
     return npp * S * S;
 }
 
+// Rounds of the wave kernel for runs of up to n positions: nch chunks of R positions, R
+// one of the compiled sizes (KR_WAVE_R).  A chunk costs its rounds and one frontier filter,
+// which takes about as long as two rounds (11 % of the kernel where a chunk has 17).
+struct WaveRounds {
+    int R, nch;
+    int cost() const { return nch * (R + 2); }
+};
+
+WaveRounds wave_rounds(int n)
+{
+    WaveRounds best{0, 0};
+    for (int R : {KR_WAVE_R}) {
+        const WaveRounds w{R, (n + R - 1) / R};
+        if (!best.R || w.cost() < best.cost()) best = w;
+    }
+    return best;
+}
+
 // One comm kernel and at most 64 SM choices: one wave per slab.  Lane (h, s) takes SM
 // choice s and the h-th run of launch positions, R of them per register chunk.
 bool wave_plan(EvalArgs *a)
@@ -61,15 +79,22 @@ bool wave_plan(EvalArgs *a)
     a->w_pw = (int)rows16;
     a->w_a0 = (int)(2 * rows16);
     a->lds_doubles = (int)lds;
-    // runs of span positions, a multiple of 8 when there are several (the running-sum
-    // pass keeps a lane's starting sums at 8-row block boundaries); the last run takes
-    // the rest
+    // Runs of span positions, the last one taking the rest.  A wave walks as many rounds
+    // as the longest run has positions (rounded up to whole chunks of R), so the runs are
+    // as even as they can be; runs that start at multiples of 8 save the running-sum pass
+    // a look inside its 8-row blocks and are taken where they cost no round.
     a->H = 64 / a->S;
-    a->span = a->H == 1 ? a->n_pos : std::max(8, a->n_pos / a->H / 8 * 8);
+    auto longest = [&](int span) {
+        return std::max(std::min(span, a->n_pos), a->n_pos - (a->H - 1) * span);
+    };
+    const int span8 = a->H == 1 ? a->n_pos : std::max(8, a->n_pos / a->H / 8 * 8);
+    const int span1 = (a->n_pos + a->H - 1) / a->H;
+    const WaveRounds w8 = wave_rounds(longest(span8)), w1 = wave_rounds(longest(span1));
+    const bool even = w1.cost() < w8.cost();
+    a->span = even ? span1 : span8;
+    a->R = even ? w1.R : w8.R;
+    a->nch = even ? w1.nch : w8.nch;
     const int last = std::max(0, a->n_pos - (a->H - 1) * a->span);
-    const int maxrun = std::max(std::min(a->span, a->n_pos), last);
-    a->R = maxrun <= 2 ? 2 : maxrun <= 4 ? 4 : maxrun <= 8 ? 8 : 17;
-    a->nch = (maxrun + a->R - 1) / a->R;
     a->fixed32 = a->N == 32 && a->S == 32 && a->n_pos == 33 && a->H == 2 && a->span == 16 &&
                  a->R == 17 && a->nch == 1 && std::min(a->span, last) >= a->R - 1 &&
                  a->w_pw == KR_FIX32_PW && a->w_a0 == 2 * KR_FIX32_PW;

@@ -76,8 +76,10 @@ __device__ __forceinline__ void finish_tail(const Tail &q, double p_static, doub
 // runs past the last kernel stops by itself.  SC > 0 fixes the number of SM choices at
 // compile time (row offsets become immediates).
 //
-// Lane (h, s) takes positions [plo, phi): runs of `span` positions (a multiple of 8
-// when there are several runs), the last run taking the rest.  Round r of a chunk
+// Lane (h, s) takes positions [plo, phi): runs of `span` positions, the last run taking
+// the rest.  A wave's time is its rounds, the positions of the longest run: with runs at
+// multiples of 8 only, 42 positions x 19 SM choices took 34 rounds (runs of 8, 8 and 26 in
+// chunks of 17) where 14 do.  Round r of a chunk
 // evaluates position c0 + r of every lane.  Its end-cursor search reads a batch of K
 // rows loaded one round earlier; the loads for its tail and for the next round are
 // issued right after the search, and the previous round's tail is finished while they
@@ -142,7 +144,7 @@ __global__ void __launch_bounds__(64) eval_filter_wave_kernel(EvalArgs a, UnitOu
 
         // Running sums, 8 rows at a time: every lane sums its column (lane 0 the all-SM
         // column, writing the records; the others their comm-time column) and keeps the
-        // sums at its first position, which is a multiple of 8 (or 0).
+        // sums at its first position.
         double pA = 0.0, pB = 0.0, a0, b0;
         {
             const int cc = lane == 0 ? 0 : sg;
@@ -175,6 +177,14 @@ __global__ void __launch_bounds__(64) eval_filter_wave_kernel(EvalArgs a, UnitOu
                 if (i0 + 8 == plo) {
                     pA = sa;
                     pB = sb;
+                }
+                if (!FX && __ballot(plo > i0 && plo < i0 + 8)) {  // a run starts inside
+#pragma unroll
+                    for (int q = 1; q < 8; ++q)
+                        if (i0 + q == plo) {
+                            pA = ra[q];
+                            pB = rb[q];
+                        }
                 }
                 if (lane == 0) {
                     double *c = (double *)(C0 + i0);
@@ -339,22 +349,20 @@ static void launch_wave_r(const EvalArgs &a, const UnitOut &o, size_t lds, hipSt
         hipLaunchKernelGGL((eval_filter_wave_kernel<R, 4, SC, FX>), grid, block, lds, st, a, o);
 }
 
+// The general instance of a.R positions per chunk; false if it is none of Rs.
+template <int... Rs>
+static bool launch_wave_any(const EvalArgs &a, const UnitOut &o, size_t lds, hipStream_t st)
+{
+    return ((a.R == Rs && (launch_wave_r<Rs, 0>(a, o, lds, st), true)) || ...);
+}
+
 hipError_t launch_eval_filter_wave(const EvalArgs &a, const UnitOut &o, hipStream_t st)
 {
     const size_t lds = (size_t)a.lds_doubles * sizeof(double);
     if (a.S == 32 && a.R == 17 && a.fixed32) launch_wave_r<17, 32, true>(a, o, lds, st);
     else if (a.S == 32 && a.R == 17) launch_wave_r<17, 32>(a, o, lds, st);
-    else if (a.S == 16 && a.R == 8) launch_wave_r<8, 16>(a, o, lds, st);
-    else if (a.S == 8 && a.R == 8) launch_wave_r<8, 8>(a, o, lds, st);
-    else {
-        switch (a.R) {
-        case 2: launch_wave_r<2, 0>(a, o, lds, st); break;
-        case 4: launch_wave_r<4, 0>(a, o, lds, st); break;
-        case 8: launch_wave_r<8, 0>(a, o, lds, st); break;
-        case 17: launch_wave_r<17, 0>(a, o, lds, st); break;
-        default: return hipErrorInvalidValue;
-        }
-    }
+    else if (a.S == 16 && a.R == 7) launch_wave_r<7, 16>(a, o, lds, st);
+    else if (!launch_wave_any<KR_WAVE_R>(a, o, lds, st)) return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -10,6 +10,9 @@
 #define KR_PAIR_WAVES 4    // waves per block of the two-comm evaluation kernel
 #define KR_FIN_UNITS 2048  // units per segment the finalize kernel's LDS path takes
 #define KR_TILE 2048       // points per tile of the stand-alone filter
+// Positions per chunk that the wave kernel is compiled for.  Runs of 1 to 8 positions get
+// their own size, longer ones waste one round at most (three above 14).
+#define KR_WAVE_R 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 17
 #define KR_PAD 3           // rows the wave kernel's end-cursor search reads per step
 // Power-slab offset (doubles) of the one-wave layout with 32 kernels and 32 SM choices:
 // t slab and pad rows, rounded up to keep the second table 16-byte aligned.
