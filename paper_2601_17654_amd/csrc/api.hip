@@ -769,13 +769,27 @@ kr_status kr_uncertainty(int32_t n_members, int64_t n, const double *T_m, const 
                : KR_EHIP;
 }
 
+// Rows per wave of the selection's tiles: a power of two, large where that still leaves
+// 1,024 tiles (four blocks for every CU; larger tiles sort less often per candidate), small
+// for small batches, which otherwise leave most of the chip idle (64 partitions of 25,600
+// candidates: one tile each, 268 us; tiles of 2,048, 38 us).
+static int select_rows(int64_t n_cand)
+{
+    int rows = KR_SEL_ROWS_MAX;
+    while (rows > KR_SEL_ROWS_MIN && n_cand / (rows * KR_BLOCK) < 1024) rows /= 2;
+    return rows;
+}
+
 size_t kr_select_batch_workspace(int32_t n_seg, int64_t n_cand)
 {
     if (n_seg < 1 || n_cand < 0) return 0;
-    const int64_t tiles = n_cand / KR_SEL_TILE + n_seg;
+    const int64_t tiles = n_cand / (select_rows(n_cand) * KR_BLOCK) + n_seg;
     Carve c(nullptr);
     c.take<int64_t>(n_seg + 1);
     c.take<int32_t>(1);
+    c.take<double>(4 * (int64_t)n_seg);
+    c.take<int32_t>(4 * (int64_t)n_seg);
+    c.take<int32_t>(tiles);
     c.take<uint64_t>(tiles * 4 * KR_SEL_LIST);
     c.take<int32_t>(tiles * 4 * KR_SEL_LIST);
     return c.used;
@@ -807,9 +821,13 @@ kr_status kr_select_batch(int32_t n_seg, int64_t n_cand, const int64_t *cand_off
     a.k[2] = k3;
     a.k[3] = k;
     a.npass = unc ? 4 : 3;
-    a.max_tiles = n_cand / KR_SEL_TILE + n_seg;
+    a.rows = select_rows(n_cand);
+    a.max_tiles = n_cand / (a.rows * KR_BLOCK) + n_seg;
     a.tile_off = c.take<int64_t>(n_seg + 1);
     a.flag = c.take<int32_t>(1);
+    a.floor_v = c.take<double>(4 * (int64_t)n_seg);
+    a.floor_i = c.take<int32_t>(4 * (int64_t)n_seg);
+    a.tile_seg = c.take<int32_t>(a.max_tiles);
     a.part_key = c.take<uint64_t>(a.max_tiles * 4 * KR_SEL_LIST);
     a.part_idx = c.take<int32_t>(a.max_tiles * 4 * KR_SEL_LIST);
     a.sel = sel_out;

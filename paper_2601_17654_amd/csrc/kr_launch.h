@@ -201,7 +201,8 @@ hipError_t launch_mb_enum_gather(const MbArgs &a, const int64_t *base, const int
 // mbo.hip: scores and batch selection of the Bayesian optimisation (Section 4.3,
 // Algorithm 1).
 #define KR_HVI_TILE 1024  // candidates per block of the score kernel
-#define KR_SEL_TILE 32768  // candidates per block of the selection tile kernel
+#define KR_SEL_ROWS_MIN 8    // rows of 64 candidates per wave of the selection tile kernel
+#define KR_SEL_ROWS_MAX 128
 #define KR_SEL_LIST 64    // entries of a wave's top list (one per lane)
 
 struct HviArgs {
@@ -226,9 +227,13 @@ struct SelArgs {
     const double *score, *unc;  // unc == nullptr: no exploration pass
     int32_t k[4];               // k1, k2, k3, k
     int npass;                  // 3 or 4
+    int rows;                   // rows per wave: a tile is rows * KR_BLOCK candidates
     int64_t max_tiles;          // launch bound on the selection tiles
     int64_t *tile_off;          // [n_seg + 1]
     int32_t *flag;              // [1] set when a score is NaN
+    double *floor_v;            // [n_seg][4] a pass's best k_p of the partition reach this
+    int32_t *floor_i;           // [n_seg][4] score, with this index or a smaller one on a tie
+    int32_t *tile_seg;          // [max_tiles] partition of each tile
     uint64_t *part_key;         // [max_tiles][npass][KR_SEL_LIST]
     int32_t *part_idx;
     int64_t *sel;               // [n_seg][k]
