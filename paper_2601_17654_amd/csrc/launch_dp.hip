@@ -17,7 +17,16 @@
 //     with a smaller time;
 //   * the kept points go to an LDS arena with their back-pointer (source, point).
 // The schedules of P(0, 0) are then walked back one lane per point.
+//
+// Most cells have a handful of candidates (4 on average on two 11-op sequences, 98.9 % have
+// at most 16), so the first pass packs four instances into a wave, one per row of 16 lanes:
+// the cells, their slots and their order are the same for all of them, only the counts
+// differ.  Sources, scans and comparisons stay inside a row and use its DPP broadcasts.
+// The instances that need more than their share are solved again, one per wave as above.
 #include <math.h>
+
+#include <type_traits>
+#include <utility>
 
 #include "kr_device.h"
 #include "kr_launch.h"
@@ -364,6 +373,333 @@ __device__ bool dp_solve(const DpArgs &a, int64_t inst, char *lds, int arena, in
     return true;
 }
 
+// ---- four instances per wave -----------------------------------------------------------
+
+// Lane Y of every row of 16, in all lanes of the row.
+template <int Y>
+__device__ __forceinline__ int row_bcast(int x)
+{
+    return __builtin_amdgcn_update_dpp(0, x, 0x150 + Y, 0xF, 0xF, false);  // row_newbcast
+}
+template <int Y>
+__device__ __forceinline__ double row_bcast(double x)
+{
+    const uint64_t b = dbits(x);
+    const uint32_t lo = (uint32_t)row_bcast<Y>((int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)row_bcast<Y>((int)(uint32_t)(b >> 32));
+    return bitsd(((uint64_t)hi << 32) | lo);
+}
+template <int D>
+__device__ __forceinline__ int row_add_below(int x)  // x plus lane - D's x (0 past the row)
+{
+    return x + __builtin_amdgcn_update_dpp(0, x, 0x110 + D, 0xF, 0xF, false);  // row_shr
+}
+
+// f(0), f(1), ... f(15) with compile-time arguments, as long as they are below n (uniform).
+template <typename F, int... Y>
+__device__ __forceinline__ void row_for(int n, F f, std::integer_sequence<int, Y...>)
+{
+    ((Y < n && (f(std::integral_constant<int, Y>()), true)) && ...);
+}
+template <typename F>
+__device__ __forceinline__ void row_for(int n, F f)
+{
+    row_for(n, f, std::make_integer_sequence<int, 16>());
+}
+
+// Byte offsets of the LDS of one wave of four instances: their operations, the points of
+// all their cells (one pool) and each cell's (first point << 8 | points).
+struct DpQuadLds {
+    int ops, arT, arE, arB, cell, bytes;
+};
+
+__host__ __device__ inline DpQuadLds dp_quad_lds(int nops, int ncell, int pool)
+{
+    DpQuadLds l;
+    int o = 0;
+    auto take = [&](int bytes) {
+        const int at = o;
+        o += (bytes + 7) / 8 * 8;
+        return at;
+    };
+    l.ops = take(4 * 32 * nops);
+    l.arT = take(8 * pool);
+    l.arE = take(8 * pool);
+    l.cell = take(4 * 4 * ncell);
+    l.arB = take(2 * pool);
+    l.bytes = o;
+    return l;
+}
+
+// Keeps candidate c (this lane's, `mine`) unless one before it in (T, E, index) order has
+// energy at or below its own; y is the other one's index.
+__device__ __forceinline__ bool dp_beaten(double ty, double ey, int y, double t, double e, int c)
+{
+    return ty <= t && ey <= e && !(ty == t && ey == e && y >= c);
+}
+
+// The points of four instances fill up to 40 KB of LDS, so only four such groups share a
+// compute unit, and a cell is one chain of LDS reads, row scans and compares.  The cells of an
+// antidiagonal need only later antidiagonals, so KR_DP_QW waves share the group's LDS and
+// take them in turn, a barrier between antidiagonals.  65,536 instances of two 11-op
+// sequences: 6.8 ms with one instance per wave, 2.7 ms with one wave per four, 1.4 ms so.
+#define KR_DP_QW 4
+
+struct QuadShared {
+    int32_t used;  // pool points in use (may pass the pool's end)
+    int32_t dead;  // bit q: instance q needs more than its share
+};
+
+// The instances of group `grp`: 4 * grp .. 4 * grp + 3 of all, or of the first queue; the
+// ones that need more (points than the pool holds, or more than 64 candidates in a cell; 128
+// from the queue) go on the first queue, or from there on the second.
+template <bool QUEUED>
+__device__ __forceinline__ void dp_quad(const DpArgs &a, int64_t grp, int64_t n, int pool,
+                                        char *lds, QuadShared &sh)
+{
+    const int lane = threadIdx.x & 63, row = lane >> 4, r = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int H = QUEUED ? 8 : 4;  // candidates per lane at most
+    const int nops = a.I + a.J, W = a.J + 1, ncell = (a.I + 1) * W;
+    const DpQuadLds L = dp_quad_lds(nops, ncell, pool);
+    double *const ops4 = (double *)(lds + L.ops);
+    double *const arT = (double *)(lds + L.arT), *const arE = (double *)(lds + L.arE);
+    int16_t *const arB = (int16_t *)(lds + L.arB);
+    int32_t *const cell = (int32_t *)(lds + L.cell) + row * ncell;
+    const int64_t inst0 = grp * 4;
+    const bool there = inst0 + row < n;  // row-uniform
+    const int64_t inst = !there ? 0 : QUEUED ? a.retry[inst0 + row] : inst0 + row;
+    const double *const ops = ops4 + 4 * nops * row;
+    {
+        // a row with no instance solves a copy of another's numbers, and writes nothing
+        const double *const src = a.ops + inst * 4 * nops;
+        for (int x = wave * 16 + r; x < 4 * nops; x += 16 * KR_DP_QW)
+            ops4[4 * nops * row + x] = src[x];
+    }
+    if (threadIdx.x == 0) {
+        arT[0] = 0.0;
+        arE[0] = 0.0;
+        arB[0] = -1;
+        sh.used = 1;
+        sh.dead = 0;
+    }
+    if (wave == 0 && r == 0) cell[ncell - 1] = 1;  // P(I, J) = {(0, 0)}, one point for all four
+    // lane o: kind and run of op o of each sequence (reading them from the arguments by a
+    // varying index would be a memory access per cell)
+    const int seq1 = lane < a.I ? a.kind[lane] | a.run1[lane] << 1 : 0;
+    const int seq2 = lane < a.J ? a.kind[a.I + lane] | a.run2[lane] << 1 : 0;
+    bool dead = !there;  // row-uniform
+    const uint64_t row_bits = 0xFFFFull << (16 * row);
+    for (int d = a.I + a.J - 1; d >= 0; --d) {
+        __syncthreads();  // the later antidiagonals' cells are in LDS
+        dead = dead || (sh.dead >> row & 1);
+        const int i1 = min(a.I, d);
+        for (int i = max(0, d - a.J) + wave; i <= i1; i += KR_DP_QW) {
+            const int j = d - i;
+            const int k1 = lane_i32(seq1, i), k2 = lane_i32(seq2, j);
+            Slots s;
+            s.va = i < a.I;
+            s.vb = j < a.J;
+            s.nc = k1 & 1 ? min(a.kmax, k2 >> 1) : 0;
+            s.nd = k2 & 1 ? min(a.kmax, k1 >> 1) : 0;
+            const int ns = s.va + s.vb + s.nc + s.nd;  // at most 16 (the launch checks)
+            // lane r of a row = source r, in canonical order (nc and nd are never both set)
+            double gT = 0.0, gE = 0.0;
+            int succ = 0;
+            {
+                const bool isb = r >= s.va;  // the alone op of S2, and overlaps below
+                const int k = r - s.va - s.vb + 1;
+                const int ni = k >= 1 ? (s.nc ? i + 1 : i + k) : (isb ? i : i + 1);
+                const int nj = k >= 1 ? (s.nc ? j + k : j + 1) : (isb ? j + 1 : j);
+                if (r < ns) succ = cell[ni * W + nj];
+                if (k < 1)
+                    dp_alone(ops + 4 * (isb ? a.I + j : i), a.p_static, &gT, &gE);
+                else if (r < ns)
+                    dp_group(ops, s.nc ? i : a.I + j, s.nc ? a.I + j : i, k, a.p_static, &gT, &gE);
+            }
+            const int n_succ = dead ? 0 : succ & 0xFF, st = succ >> 8;
+            int inc = row_add_below<1>(n_succ);
+            inc = row_add_below<2>(inc);
+            inc = row_add_below<4>(inc);
+            inc = row_add_below<8>(inc);
+            const int ex = inc - n_succ;  // first candidate of this lane's source
+            int C = row_bcast<15>(inc);   // candidates of this row's cell
+            if (C > 16 * H) {
+                dead = true;
+                C = 0;
+            }
+            const int Cm = max(max(lane_i32(C, 0), lane_i32(C, 16)),
+                               max(lane_i32(C, 32), lane_i32(C, 48)));
+            if (Cm <= 16) {
+                // one candidate per lane
+                double t = 0.0, e = 0.0;
+                int lo = 0, at = 0, first = 0;
+                row_for(ns, [&](auto y) {
+                    constexpr int Y = decltype(y)::value;
+                    const int exy = row_bcast<Y>(ex), sty = row_bcast<Y>(st);
+                    const double Ty = row_bcast<Y>(gT), Ey = row_bcast<Y>(gE);
+                    if (exy <= r) {
+                        lo = Y;
+                        at = sty;
+                        first = exy;
+                        t = Ty;
+                        e = Ey;
+                    }
+                });
+                const int q = r - first;
+                const bool live = r < C;
+                t = live ? t + arT[at + q] : INFINITY;
+                e = live ? e + arE[at + q] : INFINITY;
+                bool k = live;
+                row_for(Cm, [&](auto y) {
+                    constexpr int Y = decltype(y)::value;
+                    const double ty = row_bcast<Y>(t), ey = row_bcast<Y>(e);
+                    if (dp_beaten(ty, ey, Y, t, e, r)) k = false;
+                });
+                // pool places: rows in order, kept points of a row by time (distinct)
+                const uint64_t km = __ballot(k);
+                const int kept = __popcll(km & row_bits);
+                int used = 0;
+                if (lane == 0) used = atomicAdd(&sh.used, __popcll(km));
+                const double tk = k ? t : INFINITY;
+                int rank = 0;
+                row_for(Cm, [&](auto y) {
+                    constexpr int Y = decltype(y)::value;
+                    rank += row_bcast<Y>(tk) < t ? 1 : 0;
+                });
+                used = lane_i32(used, 0);
+                const int b = used + __popcll(km & ((1ull << (16 * row)) - 1));
+                const bool fits = b + kept <= pool;
+                if (!fits) dead = true;
+                if (k && fits) {
+                    arT[b + rank] = t;
+                    arE[b + rank] = e;
+                    arB[b + rank] = (int16_t)(lo * 64 + q);
+                }
+                if (r == 0) cell[i * W + j] = fits ? b << 8 | kept : 0;
+            } else {
+                // up to H candidates per lane: c = r, r + 16, ...
+                double t[H], e[H];
+                int lo[H], q[H];
+                const int rb = lane & 48;
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    const int c = r + 16 * h;
+                    int src = 0, first = 0;
+                    for (int y = 0; y < ns; ++y) {
+                        const int exy = __shfl(ex, rb + y, 64);
+                        if (exy <= c) {
+                            src = y;
+                            first = exy;
+                        }
+                    }
+                    lo[h] = src;
+                    q[h] = c - first;
+                    const double Ty = bitsd(shfl_u64(dbits(gT), rb + src));
+                    const double Ey = bitsd(shfl_u64(dbits(gE), rb + src));
+                    const int at = __shfl(st, rb + src, 64) + q[h];
+                    t[h] = c < C ? Ty + arT[at] : INFINITY;
+                    e[h] = c < C ? Ey + arE[at] : INFINITY;
+                }
+                bool k[H];
+#pragma unroll
+                for (int h = 0; h < H; ++h) k[h] = r + 16 * h < C;
+#pragma unroll
+                for (int g = 0; g < H; ++g)
+                    for (int y = 0; y < 16 && 16 * g + y < Cm; ++y) {
+                        const double ty = bitsd(shfl_u64(dbits(t[g]), rb + y));
+                        const double ey = bitsd(shfl_u64(dbits(e[g]), rb + y));
+#pragma unroll
+                        for (int h = 0; h < H; ++h)
+                            if (dp_beaten(ty, ey, 16 * g + y, t[h], e[h], r + 16 * h)) k[h] = false;
+                    }
+                int kept = 0, before = 0, rank[H] = {};
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    const uint64_t km = __ballot(k[h]);
+                    kept += __popcll(km & row_bits);
+                    before += __popcll(km & ((1ull << (16 * row)) - 1));
+                }
+#pragma unroll
+                for (int g = 0; g < H; ++g) {
+                    const double tk = k[g] ? t[g] : INFINITY;
+                    for (int y = 0; y < 16 && 16 * g + y < Cm; ++y) {
+                        const double ty = bitsd(shfl_u64(dbits(tk), rb + y));
+#pragma unroll
+                        for (int h = 0; h < H; ++h) rank[h] += ty < t[h] ? 1 : 0;
+                    }
+                }
+                int used = 0;
+                if (lane == 63) used = atomicAdd(&sh.used, before + kept);  // all four rows'
+                used = lane_i32(used, 63);
+                const int b = used + before;
+                const bool fits = kept <= KR_DP_CELL_CAP && b + kept <= pool;
+                if (!fits) dead = true;
+                if (fits)
+#pragma unroll
+                    for (int h = 0; h < H; ++h)
+                        if (k[h]) {
+                            arT[b + rank[h]] = t[h];
+                            arE[b + rank[h]] = e[h];
+                            arB[b + rank[h]] = (int16_t)(lo[h] * 64 + q[h]);
+                        }
+                if (r == 0) cell[i * W + j] = fits ? b << 8 | kept : 0;
+            }
+            if (dead && r == 0 && there) atomicOr(&sh.dead, 1 << row);
+        }
+    }
+    __syncthreads();
+    if (!there) return;
+    if (sh.dead >> row & 1) {
+        if (wave == 0 && r == 0) {
+            a.out_n[inst] = -1;
+            int32_t *const queue = a.retry + (QUEUED ? a.n_inst : 0);
+            queue[atomicAdd(a.retry_n + (QUEUED ? 1 : 0), 1)] = (int32_t)inst;
+        }
+        return;
+    }
+    const int n0 = cell[0] & 0xFF;
+    if (wave == 0 && r == 0) a.out_n[inst] = n0;
+    for (int p = wave * 16 + r; p < min(n0, a.out_cap); p += 16 * KR_DP_QW) {
+        const int64_t o = inst * a.out_cap + p;
+        a.out_T[o] = arT[(cell[0] >> 8) + p];
+        a.out_E[o] = arE[(cell[0] >> 8) + p];
+        if (a.out_sched) {
+            int32_t *sc = a.out_sched + o * nops;
+            int ci = 0, cj = 0, cq = p, d = 0;
+            while (!(ci == a.I && cj == a.J) && d < nops) {
+                const int b = arB[(cell[ci * W + cj] >> 8) + cq];
+                int ni, nj;
+                sc[d++] = dp_decode(a, ci, cj, b / 64, &ni, &nj);
+                ci = ni;
+                cj = nj;
+                cq = b % 64;
+            }
+            for (; d < nops; ++d) sc[d] = -1;
+        }
+    }
+}
+
+__global__ void __launch_bounds__(64 * KR_DP_QW) dp_quad_kernel(DpArgs a, int pool)
+{
+    extern __shared__ double dp_smem[];
+    __shared__ QuadShared sh;
+    dp_quad<false>(a, blockIdx.x, a.n_inst, pool, (char *)dp_smem, sh);
+}
+
+// The queued instances, four to a block with a larger pool (a block for an instance alone
+// would take as long).
+__global__ void __launch_bounds__(64 * KR_DP_QW) dp_quad_retry_kernel(DpArgs a, int pool)
+{
+    extern __shared__ double dp_smem[];
+    __shared__ QuadShared sh;
+    const int64_t n = a.retry_n[0];
+    for (int64_t grp = blockIdx.x; grp * 4 < n; grp += gridDim.x) {
+        dp_quad<true>(a, grp, n, pool, (char *)dp_smem, sh);
+        __syncthreads();
+    }
+}
+
 __global__ void dp_init_kernel(int32_t *status, int32_t *retry_n)
 {
     *status = KR_OK;
@@ -410,15 +746,37 @@ hipError_t launch_dp(const DpArgs &a, hipStream_t st)
     hipLaunchKernelGGL(dp_init_kernel, dim3(1), dim3(1), 0, st, a.status, a.retry_n);
     if (a.n_inst > 0) {
         const int nops = a.I + a.J, ncell = (a.I + 1) * (a.J + 1);
-        const int small = dp_lds(nops, ncell, a.arena_s, a.cand_s).bytes;
-        hipLaunchKernelGGL(dp_first_kernel, dim3((unsigned)a.n_inst), dim3(64), small, st, a);
-        // middle budget: still several instances per compute unit; then the full one
-        const int am = KR_DP_ARENA / 2, cm = KR_DP_CAND / 4;
-        const int mid = dp_lds(nops, ncell, am, cm).bytes;
-        const int big = dp_lds(nops, ncell, KR_DP_ARENA, KR_DP_CAND).bytes;
-        const int64_t g1 = a.n_inst < 2048 ? a.n_inst : 2048;
+        // a cell has at most two lone ops and one run of overlaps as its sources: a row of
+        // 16 lanes takes runs of up to 14
+        int run = 0;
+        for (int i = 0; i <= a.I; ++i) run = a.run1[i] > run ? a.run1[i] : run;
+        for (int j = 0; j <= a.J; ++j) run = a.run2[j] > run ? a.run2[j] : run;
         const int64_t g2 = a.n_inst < 512 ? a.n_inst : 512;
-        hipLaunchKernelGGL(dp_retry_kernel, dim3((unsigned)g1), dim3(64), mid, st, a, 0, am, cm);
+        if (2 + (a.kmax < run ? a.kmax : run) <= 16) {
+            // As many points as let the four groups that the registers allow share a compute
+            // unit (40 KB each); what does not fit is solved again with 64 KB.  Two 11-op
+            // sequences: 796 points a group on average, 1,969 at most of 1,500 groups.  A
+            // pool of 1,296 sent 2 % of the instances to one-wave solvers, which took 0.76 ms
+            // however few they were.
+            const int fixed = 64 + dp_quad_lds(nops, ncell, 0).bytes;
+            const int room = (40 * 1024 - fixed) / 18 & ~3, most = (64 * 1024 - fixed) / 18 & ~3;
+            const int pool = room < 1024 ? 1024 : room < 16 * ncell ? room : 16 * ncell;
+            const int64_t groups = (a.n_inst + 3) / 4;
+            hipLaunchKernelGGL(dp_quad_kernel, dim3((unsigned)groups), dim3(64 * KR_DP_QW),
+                               dp_quad_lds(nops, ncell, pool).bytes, st, a, pool);
+            hipLaunchKernelGGL(dp_quad_retry_kernel, dim3((unsigned)(groups < 512 ? groups : 512)),
+                               dim3(64 * KR_DP_QW), dp_quad_lds(nops, ncell, most).bytes, st, a,
+                               most);
+        } else {
+            const int small = dp_lds(nops, ncell, a.arena_s, a.cand_s).bytes;
+            hipLaunchKernelGGL(dp_first_kernel, dim3((unsigned)a.n_inst), dim3(64), small, st, a);
+            // middle budget: still several instances per compute unit; then the full one
+            const int am = KR_DP_ARENA / 2, cm = KR_DP_CAND / 4;
+            const int mid = dp_lds(nops, ncell, am, cm).bytes;
+            const int64_t g1 = a.n_inst < 2048 ? a.n_inst : 2048;
+            hipLaunchKernelGGL(dp_retry_kernel, dim3((unsigned)g1), dim3(64), mid, st, a, 0, am, cm);
+        }
+        const int big = dp_lds(nops, ncell, KR_DP_ARENA, KR_DP_CAND).bytes;
         hipLaunchKernelGGL(dp_retry_kernel, dim3((unsigned)g2), dim3(64), big, st, a, 1,
                            KR_DP_ARENA, KR_DP_CAND);
     }
