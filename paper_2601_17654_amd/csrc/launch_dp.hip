@@ -379,7 +379,9 @@ __device__ bool dp_solve(const DpArgs &a, int64_t inst, char *lds, int arena, in
 template <int Y>
 __device__ __forceinline__ int row_bcast(int x)
 {
-    return __builtin_amdgcn_update_dpp(0, x, 0x150 + Y, 0xF, 0xF, false);  // row_newbcast
+    // row_newbcast; every lane has a source, so no old value is set up (VALU issue bounds the
+    // kernel, and that move doubled the broadcasts)
+    return __builtin_amdgcn_mov_dpp(x, 0x150 + Y, 0xF, 0xF, false);
 }
 template <int Y>
 __device__ __forceinline__ double row_bcast(double x)
