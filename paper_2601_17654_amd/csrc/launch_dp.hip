@@ -444,7 +444,7 @@ __device__ __forceinline__ bool dp_beaten(double ty, double ey, int y, double t,
 // compute unit, and a cell is one chain of LDS reads, row scans and compares.  The cells of an
 // antidiagonal need only later antidiagonals, so KR_DP_QW waves share the group's LDS and
 // take them in turn, a barrier between antidiagonals.  65,536 instances of two 11-op
-// sequences: 6.8 ms with one instance per wave, 2.7 ms with one wave per four, 1.4 ms so.
+// sequences: 6.8 ms with one instance per wave, 2.7 ms with one wave per four, 1.3 ms so.
 #define KR_DP_QW 4
 
 struct QuadShared {
@@ -532,121 +532,114 @@ __device__ __forceinline__ void dp_quad(const DpArgs &a, int64_t grp, int64_t n,
             }
             const int Cm = max(max(lane_i32(C, 0), lane_i32(C, 16)),
                                max(lane_i32(C, 32), lane_i32(C, 48)));
-            if (Cm <= 16) {
-                // one candidate per lane
-                double t = 0.0, e = 0.0;
-                int lo = 0, at = 0, first = 0;
-                row_for(ns, [&](auto y) {
-                    constexpr int Y = decltype(y)::value;
-                    const int exy = row_bcast<Y>(ex), sty = row_bcast<Y>(st);
-                    const double Ty = row_bcast<Y>(gT), Ey = row_bcast<Y>(gE);
-                    if (exy <= r) {
-                        lo = Y;
-                        at = sty;
-                        first = exy;
-                        t = Ty;
-                        e = Ey;
+            // up to NH candidates per lane: c = r, r + 16, ...
+            auto solve = [&](auto nh) {
+                constexpr int NH = decltype(nh)::value;
+                const int rb = lane & 48;
+                double t[NH], e[NH];
+                int lo[NH], q[NH], at[NH];
+#pragma unroll
+                for (int h = 0; h < NH; ++h) lo[h] = q[h] = at[h] = 0;
+                if constexpr (NH <= 2) {
+                    row_for(ns, [&](auto y) {
+                        constexpr int Y = decltype(y)::value;
+                        const int exy = row_bcast<Y>(ex), sty = row_bcast<Y>(st);
+                        const double Ty = row_bcast<Y>(gT), Ey = row_bcast<Y>(gE);
+#pragma unroll
+                        for (int h = 0; h < NH; ++h)
+                            if (exy <= r + 16 * h) {
+                                lo[h] = Y;
+                                q[h] = r + 16 * h - exy;
+                                at[h] = sty;
+                                t[h] = Ty;
+                                e[h] = Ey;
+                            }
+                    });
+                } else {
+#pragma unroll
+                    for (int h = 0; h < NH; ++h) {
+                        if (16 * h >= Cm) break;
+                        for (int y = 0; y < ns; ++y) {
+                            const int exy = __shfl(ex, rb + y, 64);
+                            if (exy <= r + 16 * h) {
+                                lo[h] = y;
+                                q[h] = r + 16 * h - exy;
+                            }
+                        }
+                        t[h] = bitsd(shfl_u64(dbits(gT), rb + lo[h]));
+                        e[h] = bitsd(shfl_u64(dbits(gE), rb + lo[h]));
+                        at[h] = __shfl(st, rb + lo[h], 64);
                     }
-                });
-                const int q = r - first;
-                const bool live = r < C;
-                t = live ? t + arT[at + q] : INFINITY;
-                e = live ? e + arE[at + q] : INFINITY;
-                bool k = live;
-                row_for(Cm, [&](auto y) {
-                    constexpr int Y = decltype(y)::value;
-                    const double ty = row_bcast<Y>(t), ey = row_bcast<Y>(e);
-                    if (dp_beaten(ty, ey, Y, t, e, r)) k = false;
+                }
+                bool k[NH];
+#pragma unroll
+                for (int h = 0; h < NH; ++h) {
+                    k[h] = r + 16 * h < C;
+                    t[h] = k[h] ? t[h] + arT[at[h] + q[h]] : INFINITY;
+                    e[h] = k[h] ? e[h] + arE[at[h] + q[h]] : INFINITY;
+                }
+                // f(T, E, index) of every candidate of the row
+                auto each = [&](const double (&u)[NH], const double (&v)[NH], auto f) {
+#pragma unroll
+                    for (int g = 0; g < NH; ++g) {
+                        if constexpr (NH <= 2)
+                            row_for(Cm - 16 * g, [&](auto y) {
+                                constexpr int Y = decltype(y)::value;
+                                f(row_bcast<Y>(u[g]), row_bcast<Y>(v[g]), 16 * g + Y);
+                            });
+                        else
+                            for (int y = 0; y < 16 && 16 * g + y < Cm; ++y)
+                                f(bitsd(shfl_u64(dbits(u[g]), rb + y)),
+                                  bitsd(shfl_u64(dbits(v[g]), rb + y)), 16 * g + y);
+                    }
+                };
+                each(t, e, [&](double ty, double ey, int y) {
+#pragma unroll
+                    for (int h = 0; h < NH; ++h) {
+                        if (16 * h >= Cm) break;  // uniform
+                        if (dp_beaten(ty, ey, y, t[h], e[h], r + 16 * h)) k[h] = false;
+                    }
                 });
                 // pool places: rows in order, kept points of a row by time (distinct)
-                const uint64_t km = __ballot(k);
-                const int kept = __popcll(km & row_bits);
-                int used = 0;
-                if (lane == 0) used = atomicAdd(&sh.used, __popcll(km));
-                const double tk = k ? t : INFINITY;
-                int rank = 0;
-                row_for(Cm, [&](auto y) {
-                    constexpr int Y = decltype(y)::value;
-                    rank += row_bcast<Y>(tk) < t ? 1 : 0;
-                });
-                used = lane_i32(used, 0);
-                const int b = used + __popcll(km & ((1ull << (16 * row)) - 1));
-                const bool fits = b + kept <= pool;
-                if (!fits) dead = true;
-                if (k && fits) {
-                    arT[b + rank] = t;
-                    arE[b + rank] = e;
-                    arB[b + rank] = (int16_t)(lo * 64 + q);
-                }
-                if (r == 0) cell[i * W + j] = fits ? b << 8 | kept : 0;
-            } else {
-                // up to H candidates per lane: c = r, r + 16, ...
-                double t[H], e[H];
-                int lo[H], q[H];
-                const int rb = lane & 48;
+                int kept = 0, before = 0, total = 0;
 #pragma unroll
-                for (int h = 0; h < H; ++h) {
-                    const int c = r + 16 * h;
-                    int src = 0, first = 0;
-                    for (int y = 0; y < ns; ++y) {
-                        const int exy = __shfl(ex, rb + y, 64);
-                        if (exy <= c) {
-                            src = y;
-                            first = exy;
-                        }
-                    }
-                    lo[h] = src;
-                    q[h] = c - first;
-                    const double Ty = bitsd(shfl_u64(dbits(gT), rb + src));
-                    const double Ey = bitsd(shfl_u64(dbits(gE), rb + src));
-                    const int at = __shfl(st, rb + src, 64) + q[h];
-                    t[h] = c < C ? Ty + arT[at] : INFINITY;
-                    e[h] = c < C ? Ey + arE[at] : INFINITY;
-                }
-                bool k[H];
-#pragma unroll
-                for (int h = 0; h < H; ++h) k[h] = r + 16 * h < C;
-#pragma unroll
-                for (int g = 0; g < H; ++g)
-                    for (int y = 0; y < 16 && 16 * g + y < Cm; ++y) {
-                        const double ty = bitsd(shfl_u64(dbits(t[g]), rb + y));
-                        const double ey = bitsd(shfl_u64(dbits(e[g]), rb + y));
-#pragma unroll
-                        for (int h = 0; h < H; ++h)
-                            if (dp_beaten(ty, ey, 16 * g + y, t[h], e[h], r + 16 * h)) k[h] = false;
-                    }
-                int kept = 0, before = 0, rank[H] = {};
-#pragma unroll
-                for (int h = 0; h < H; ++h) {
+                for (int h = 0; h < NH; ++h) {
                     const uint64_t km = __ballot(k[h]);
                     kept += __popcll(km & row_bits);
                     before += __popcll(km & ((1ull << (16 * row)) - 1));
-                }
-#pragma unroll
-                for (int g = 0; g < H; ++g) {
-                    const double tk = k[g] ? t[g] : INFINITY;
-                    for (int y = 0; y < 16 && 16 * g + y < Cm; ++y) {
-                        const double ty = bitsd(shfl_u64(dbits(tk), rb + y));
-#pragma unroll
-                        for (int h = 0; h < H; ++h) rank[h] += ty < t[h] ? 1 : 0;
-                    }
+                    total += __popcll(km);
                 }
                 int used = 0;
-                if (lane == 63) used = atomicAdd(&sh.used, before + kept);  // all four rows'
-                used = lane_i32(used, 63);
-                const int b = used + before;
+                if (lane == 0) used = atomicAdd(&sh.used, total);
+                double tk[NH];
+                int rank[NH];
+#pragma unroll
+                for (int h = 0; h < NH; ++h) {
+                    tk[h] = k[h] ? t[h] : INFINITY;
+                    rank[h] = 0;
+                }
+                each(tk, tk, [&](double ty, double, int) {
+#pragma unroll
+                    for (int h = 0; h < NH; ++h) {
+                        if (16 * h >= Cm) break;
+                        rank[h] += ty < t[h] ? 1 : 0;
+                    }
+                });
+                const int b = lane_i32(used, 0) + before;
                 const bool fits = kept <= KR_DP_CELL_CAP && b + kept <= pool;
                 if (!fits) dead = true;
-                if (fits)
 #pragma unroll
-                    for (int h = 0; h < H; ++h)
-                        if (k[h]) {
-                            arT[b + rank[h]] = t[h];
-                            arE[b + rank[h]] = e[h];
-                            arB[b + rank[h]] = (int16_t)(lo[h] * 64 + q[h]);
-                        }
+                for (int h = 0; h < NH; ++h)
+                    if (k[h] && fits) {
+                        arT[b + rank[h]] = t[h];
+                        arE[b + rank[h]] = e[h];
+                        arB[b + rank[h]] = (int16_t)(lo[h] * 64 + q[h]);
+                    }
                 if (r == 0) cell[i * W + j] = fits ? b << 8 | kept : 0;
-            }
+            };
+            if (Cm <= 16) solve(std::integral_constant<int, 1>());
+            else if (Cm <= 32) solve(std::integral_constant<int, 2>());
+            else solve(std::integral_constant<int, H>());
             if (dead && r == 0 && there) atomicOr(&sh.dead, 1 << row);
         }
     }
