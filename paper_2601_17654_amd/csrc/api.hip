@@ -255,14 +255,11 @@ FilterWs carve_filter(Carve &c, int64_t n_total, int n_seg, int64_t n_units, boo
 }
 
 // Union of every segment's unit frontiers, then the CSR output.
-kr_status finish_segments(const SegLayout &L, FilterWs &w, int64_t cap, int64_t *out_off,
-                          int32_t *out_idx, double *out_T, double *out_E, hipStream_t st)
+kr_status finish_segments(const SegLayout &L, FilterWs &w, const FrontierOut &o, hipStream_t st)
 {
     phase_mark(KR_PHASE_MERGE, 0, st);
-    if (launch_finalize(L, w.buf[0], w.ucnt, w.buf[1], w.fcnt, w.runcnt, w.flags, w.lists, st) !=
+    if (launch_merge(L, w.buf[0], w.ucnt, w.buf[1], w.fcnt, w.runcnt, w.flags, w.lists, o, st) !=
         hipSuccess)
-        return KR_EHIP;
-    if (launch_output(L, w.buf[1], w.fcnt, cap, out_off, out_idx, out_T, out_E, st) != hipSuccess)
         return KR_EHIP;
     phase_mark(KR_PHASE_MERGE, 1, st);
     return KR_OK;
@@ -322,14 +319,23 @@ kr_status kr_pareto_filter(int64_t n_total, const double *T, const double *E,
     L.unit_base = w.unit_base;
     L.n_seg = n_seg;
     L.unit_stride = KR_TILE;
-    if ((n_seg > 0 || status_out) &&
-        launch_tile_layout(seg_off, w.unit_base, n_seg, KR_TILE, w.lists, status_out, st) !=
+    const FrontierOut out{cap, out_off, out_idx, out_T, out_E};
+    const bool raw = pareto_raw(n_total, n_seg);
+    if ((n_seg > 0 || status_out) && !(raw && n_seg == 1) &&
+        launch_tile_layout(seg_off, w.unit_base, n_seg, KR_TILE, w.lists, w.fcnt, status_out, st) !=
             hipSuccess)
         return KR_EHIP;
+    if (raw) {
+        phase_mark(KR_PHASE_MERGE, 0, st);
+        if (launch_pareto_raw(T, E, n_total, L, w.fcnt, w.lists, out, status_out, st) != hipSuccess)
+            return KR_EHIP;
+        phase_mark(KR_PHASE_MERGE, 1, st);
+        return KR_OK;
+    }
     UnitOut o{w.buf[0].T, w.buf[0].E, w.buf[0].I, w.ucnt};
     if (n_seg > 0 && launch_pareto_tiles(T, E, L, n_units, o, status_out, st) != hipSuccess)
         return KR_EHIP;
-    return finish_segments(L, w, cap, out_off, out_idx, out_T, out_E, st);
+    return finish_segments(L, w, out, st);
 }
 
 size_t kr_evaluate_and_filter_workspace(const kr_space *space)
@@ -361,8 +367,8 @@ kr_status kr_evaluate_and_filter(const kr_space *space, const double *t, const d
     Carve c(ws);
     FilterWs w = carve_filter(c, (int64_t)a.P * a.useg, a.P, (int64_t)a.P * a.uper, true);
     a.status = status_out;
-    if (launch_uniform_layout(w.seg_off, w.unit_base, a.P, a.useg, a.uper, w.lists, status_out,
-                              st) != hipSuccess)
+    if (launch_uniform_layout(w.seg_off, w.unit_base, a.P, a.useg, a.uper, w.lists, w.fcnt,
+                              status_out, st) != hipSuccess)
         return KR_EHIP;
     UnitOut o{w.buf[0].T, w.buf[0].E, w.buf[0].I, w.ucnt};
     a.dma16 = (a.wave || a.pair) && (a.N * (a.S + 1)) % 2 == 0 && (uintptr_t)t % 16 == 0 &&
@@ -378,7 +384,7 @@ kr_status kr_evaluate_and_filter(const kr_space *space, const double *t, const d
     L.unit_base = w.unit_base;
     L.n_seg = a.P;
     L.unit_stride = a.ustride;
-    return finish_segments(L, w, cap, out_off, out_idx, out_T, out_E, st);
+    return finish_segments(L, w, FrontierOut{cap, out_off, out_idx, out_T, out_E}, st);
 }
 
 size_t kr_compose_frontiers_workspace(int32_t n_parts, int32_t n_bins)

@@ -144,11 +144,11 @@ __device__ __forceinline__ T block_exclusive(T v, T identity, Op op, T *lds, T *
     return op(before, ex);
 }
 
-template <typename T, typename Op>
+template <typename T, typename Op, int NW = KR_WAVES>
 __device__ __forceinline__ T block_reduce(T v, T identity, Op op, T *lds)
 {
     T total;
-    block_exclusive(v, identity, op, lds, &total);
+    block_exclusive<T, Op, NW>(v, identity, op, lds, &total);
     return total;
 }
 

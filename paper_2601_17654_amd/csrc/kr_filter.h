@@ -97,7 +97,9 @@ __device__ inline Key block_min_key(const Key &k, FilterShared *sh, int &parity)
     return b;
 }
 
+template <int NT = KR_BLOCK>
 __device__ inline void lds_sort_keys(uint64_t *sT, uint64_t *sE, int32_t *sI, int n);
+template <int NT = KR_BLOCK>
 __device__ inline int lds_frontier_scan(const uint64_t *sT, const uint64_t *sE, const int32_t *sI,
                                         int n, double *oT, double *oE, int32_t *oI);
 
@@ -228,6 +230,7 @@ __device__ inline int tile_frontier(const double (&vT)[CAP], const double (&vE)[
 // Sort n keys ascending in LDS with a bitonic network whose comparators all put the
 // smaller key at the lower index; positions >= n behave as +inf and never move, so n
 // need not be a power of two.  Every thread of the block must call.
+template <int NT>
 __device__ inline void lds_sort_keys(uint64_t *sT, uint64_t *sE, int32_t *sI, int n)
 {
     int m = 1, lm = 0;
@@ -239,7 +242,7 @@ __device__ inline void lds_sort_keys(uint64_t *sT, uint64_t *sE, int32_t *sI, in
         const int k = 1 << lk;
         for (int lj = lk - 1; lj >= 0; --lj) {
             const int j = 1 << lj;  // q / j and q % j by shift and mask
-            for (int q = threadIdx.x; q < (m >> 1); q += KR_BLOCK) {
+            for (int q = threadIdx.x; q < (m >> 1); q += NT) {
                 int lo, hi;
                 if (lj == lk - 1) {  // first stage of a merge: mirror within the block
                     const int blk = q >> lj, r = q & (j - 1);
@@ -266,18 +269,20 @@ __device__ inline void lds_sort_keys(uint64_t *sT, uint64_t *sE, int32_t *sI, in
 // Strict prefix-minimum scan of n sorted keys in LDS: keeps a key iff its E is below
 // every earlier E; writes the kept keys in order to oT/oE/oI and returns their count
 // (every thread).  Every thread of the block must call.
+template <int NT>
 __device__ inline int lds_frontier_scan(const uint64_t *sT, const uint64_t *sE, const int32_t *sI,
                                         int n, double *oT, double *oE, int32_t *oI)
 {
-    __shared__ uint64_t sc64[KR_WAVES];
-    __shared__ int32_t sc32[KR_WAVES];
-    const int per = (n + KR_BLOCK - 1) / KR_BLOCK;
+    __shared__ uint64_t sc64[NT / 64];
+    __shared__ int32_t sc32[NT / 64];
+    const int per = (n + NT - 1) / NT;
     const int s0 = threadIdx.x * per;
     const int s1 = min(n, s0 + per);
     uint64_t m = KR_INF_BITS;
     for (int q = s0; q < s1; ++q) m = MinU64()(m, sE[q]);
     uint64_t tot;
-    const uint64_t best0 = block_exclusive(m, (uint64_t)KR_INF_BITS, MinU64(), sc64, &tot);
+    const uint64_t best0 = block_exclusive<uint64_t, MinU64, NT / 64>(
+        m, (uint64_t)KR_INF_BITS, MinU64(), sc64, &tot);
     uint64_t best = best0;
     int nkeep = 0;
     for (int q = s0; q < s1; ++q)
@@ -286,7 +291,7 @@ __device__ inline int lds_frontier_scan(const uint64_t *sT, const uint64_t *sE, 
             best = sE[q];
         }
     int count;
-    int opos = block_exclusive(nkeep, 0, SumI32(), sc32, &count);
+    int opos = block_exclusive<int, SumI32, NT / 64>(nkeep, 0, SumI32(), sc32, &count);
     best = best0;
     for (int q = s0; q < s1; ++q) {
         const uint64_t e = sE[q];

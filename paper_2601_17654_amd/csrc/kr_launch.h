@@ -98,25 +98,36 @@ int pair_owner_host(int p1, int NW);
 hipError_t launch_decode(const DecodeArgs &d, hipStream_t st);
 
 // pareto.hip
-// Both layouts also clear lists[0], which launch_finalize expects to be zero, and write
-// KR_OK to *status when it is not NULL.
+// Both layouts also clear lists[0] and fcnt[n_seg], which launch_merge expects to be zero,
+// and write KR_OK to *status when it is not NULL.
 hipError_t launch_uniform_layout(int64_t *seg_off, int64_t *unit_base, int n_seg,
                                  int64_t seg_len, int64_t units_per_seg, int32_t *lists,
-                                 int32_t *status, hipStream_t st);
+                                 int32_t *fcnt, int32_t *status, hipStream_t st);
 hipError_t launch_tile_layout(const int64_t *seg_off, int64_t *unit_base, int n_seg, int tile,
-                              int32_t *lists, int32_t *status, hipStream_t st);
+                              int32_t *lists, int32_t *fcnt, int32_t *status, hipStream_t st);
 // status: NULL, or the input check's verdict
 hipError_t launch_pareto_tiles(const double *T, const double *E, const SegLayout &L,
                                int64_t n_units_bound, const UnitOut &o, int32_t *status,
                                hipStream_t st);
-// lists: 2 * n_seg + 2 ints of scratch, lists[0] zero on entry (cleared by the layout
-// launches above)
-hipError_t launch_finalize(const SegLayout &L, const PointBufs &buf, const int32_t *ucnt,
-                           const PointBufs &fin, int32_t *fcnt, int32_t *runcnt, uint8_t *flags,
-                           int32_t *lists, hipStream_t st);
-hipError_t launch_output(const SegLayout &L, const PointBufs &fin, const int32_t *fcnt,
-                         int64_t cap, int64_t *out_off, int32_t *out_idx, double *out_T,
-                         double *out_E, hipStream_t st);
+// CSR output of a filter: offsets [n_seg + 1], points up to element cap.
+struct FrontierOut {
+    int64_t cap;
+    int64_t *off;
+    int32_t *idx;
+    double *T, *E;
+};
+// Union of every segment's unit frontiers.  lists: 2 * n_seg + 2 ints of scratch; lists[0]
+// and fcnt[n_seg] zero on entry (cleared by the layout launches above; a single segment
+// needs neither).
+hipError_t launch_merge(const SegLayout &L, const PointBufs &buf, const int32_t *ucnt,
+                        const PointBufs &fin, int32_t *fcnt, int32_t *runcnt, uint8_t *flags,
+                        int32_t *lists, const FrontierOut &o, hipStream_t st);
+// Whether the points are few enough for one launch that sorts each segment in LDS, and that
+// launch (lists, fcnt as above; with several segments *status KR_OK on entry).
+bool pareto_raw(int64_t n_total, int n_seg);
+hipError_t launch_pareto_raw(const double *T, const double *E, int64_t n_total, const SegLayout &L,
+                             int32_t *fcnt, int32_t *lists, const FrontierOut &o, int32_t *status,
+                             hipStream_t st);
 
 // compose.hip
 struct ComposeWs {

@@ -20,13 +20,14 @@
 namespace kr {
 
 // The layout kernels also clear lists[0], the count of segments that the first merge
-// stage passes on, and the input check's verdict (so that neither needs a launch of its
+// stage passes on (or the ticket of the fused one), the segments' counts and the input check's verdict (so that neither needs a launch of its
 // own).
 __global__ void uniform_layout_kernel(int64_t *seg_off, int64_t *unit_base, int n_seg,
                                       int64_t seg_len, int64_t units_per_seg, int32_t *lists,
-                                      int32_t *status)
+                                      int32_t *fcnt, int32_t *status)
 {
     const int g = blockIdx.x * KR_BLOCK + threadIdx.x;
+    if (g < n_seg) fcnt[g] = 0;
     if (g == 0) lists[0] = 0;
     if (g == 0 && status) *status = KR_OK;
     if (g > n_seg) return;
@@ -36,20 +37,21 @@ __global__ void uniform_layout_kernel(int64_t *seg_off, int64_t *unit_base, int 
 
 hipError_t launch_uniform_layout(int64_t *seg_off, int64_t *unit_base, int n_seg,
                                  int64_t seg_len, int64_t units_per_seg, int32_t *lists,
-                                 int32_t *status, hipStream_t st)
+                                 int32_t *fcnt, int32_t *status, hipStream_t st)
 {
     hipLaunchKernelGGL(uniform_layout_kernel, dim3((n_seg + 1 + KR_BLOCK - 1) / KR_BLOCK),
                        dim3(KR_BLOCK), 0, st, seg_off, unit_base, n_seg, seg_len, units_per_seg,
-                       lists, status);
+                       lists, fcnt, status);
     return hipGetLastError();
 }
 
 // unit_base = exclusive prefix sum of ceil(len_g / tile); one block.
 __global__ void __launch_bounds__(KR_BLOCK)
 tile_layout_kernel(const int64_t *seg_off, int64_t *unit_base, int n_seg, int tile,
-                   int32_t *lists, int32_t *status)
+                   int32_t *lists, int32_t *fcnt, int32_t *status)
 {
     __shared__ int64_t sc[KR_WAVES];
+    for (int g = threadIdx.x; g < n_seg; g += KR_BLOCK) fcnt[g] = 0;
     if (threadIdx.x == 0) lists[0] = 0;
     if (threadIdx.x == 0 && status) *status = KR_OK;
     int64_t carry = 0;
@@ -69,10 +71,10 @@ tile_layout_kernel(const int64_t *seg_off, int64_t *unit_base, int n_seg, int ti
 }
 
 hipError_t launch_tile_layout(const int64_t *seg_off, int64_t *unit_base, int n_seg, int tile,
-                              int32_t *lists, int32_t *status, hipStream_t st)
+                              int32_t *lists, int32_t *fcnt, int32_t *status, hipStream_t st)
 {
     hipLaunchKernelGGL(tile_layout_kernel, dim3(1), dim3(KR_BLOCK), 0, st, seg_off, unit_base,
-                       n_seg, tile, lists, status);
+                       n_seg, tile, lists, fcnt, status);
     return hipGetLastError();
 }
 
@@ -189,13 +191,14 @@ __device__ __forceinline__ int rank_in(const double *bT, const double *bE, const
 
 // Merge staircases a = in[sa, sa+na) and b = in[sb, sb+nb) into out[sa ...); returns
 // the merged frontier's size.  Every thread of the block must call.
+template <int NT>
 __device__ inline int merge_pair(const PointBufs &in, const PointBufs &out, uint8_t *flags,
                                  int64_t sa, int na, int64_t sb, int nb)
 {
-    __shared__ int32_t sc[KR_WAVES];
+    __shared__ int32_t sc[NT / 64];
     const double *aT = in.T + sa, *aE = in.E + sa, *bT = in.T + sb, *bE = in.E + sb;
     const int32_t *aI = in.I + sa, *bI = in.I + sb;
-    for (int x = threadIdx.x; x < na + nb; x += KR_BLOCK) {
+    for (int x = threadIdx.x; x < na + nb; x += NT) {
         const bool fromA = x < na;
         const int y = fromA ? x : x - na;
         const double t = ld_l2(fromA ? aT + y : bT + y);
@@ -214,7 +217,7 @@ __device__ inline int merge_pair(const PointBufs &in, const PointBufs &out, uint
     __syncthreads();
     const int n = na + nb;
     int base = 0;
-    for (int c0 = 0; c0 < n; c0 += KR_BLOCK) {
+    for (int c0 = 0; c0 < n; c0 += NT) {
         const int x = c0 + threadIdx.x;
         const bool has = x < n;
         double t = 0.0, e = 0.0;
@@ -228,7 +231,7 @@ __device__ inline int merge_pair(const PointBufs &in, const PointBufs &out, uint
         }
         __syncthreads();
         int tot;
-        const int pos = block_exclusive(f, 0, SumI32(), sc, &tot);
+        const int pos = block_exclusive<int, SumI32, NT / 64>(f, 0, SumI32(), sc, &tot);
         if (has && f) {
             out.T[sa + base + pos] = t;
             out.E[sa + base + pos] = e;
@@ -320,32 +323,48 @@ __device__ __forceinline__ bool merge_prefix(int g, const SegLayout &L, const in
     return true;
 }
 
+// The points of a segment's units (after merge_prefix): load(q, key) for q in [q0, q1).
 template <int NT, int PER>
-__device__ __forceinline__ void merge_segment(int g, int n, const SegLayout &L,
-                                              const PointBufs &buf, const PointBufs &fin,
-                                              int32_t *fcnt, MergeLds<NT, PER> &sh)
+struct UnitPoints {
+    const MergeLds<NT, PER> &sh;
+    const PointBufs &buf;
+    int64_t s0, stride;
+    int nu;
+
+    __device__ __forceinline__ void operator()(int q0, int q1, MKey (&k)[PER]) const
+    {
+        int u = 0;  // unit holding point q0: the last u < nu with upre[u] <= q0
+#pragma unroll
+        for (int step = NT / 2; step >= 1; step >>= 1)
+            if (u + step < nu && sh.upre[u + step] <= q0) u += step;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int x = q0 + j;
+            if (x < q1) {
+                while (sh.upre[u + 1] <= x) ++u;  // skip ended and empty units (x < upre[nu])
+                const int64_t src = s0 + (int64_t)u * stride + (x - sh.upre[u]);
+                k[j] = MKey{dbits(buf.T[src]), dbits(buf.E[src]), buf.I[src]};
+            }
+        }
+    }
+};
+
+// Sorts n points (read by `points`) and writes their frontier to (oT, oE, oI)[d0 ...], where
+// d0 = place(count) is asked for once the count is known, up to element cap.
+template <int NT, int PER, typename Points, typename Place>
+__device__ __forceinline__ void merge_segment(int n, const Points &points, MergeLds<NT, PER> &sh,
+                                              double *oT, double *oE, int32_t *oI, int64_t cap,
+                                              const Place &place)
 {
     static_assert(NT * PER <= 65536 && (PER & (PER - 1)) == 0, "16-bit ids, power-of-two runs");
     const int tid = threadIdx.x;
-    const int64_t s0 = L.seg_off[g];
-    const int nu = (int)(L.unit_base[g + 1] - L.unit_base[g]);
     lds_barrier();  // upre
     const int q0 = min(n, tid * PER), q1 = min(n, q0 + PER);
     MKey k[PER];
-    int u = 0;  // unit holding point q0: the last u < nu with upre[u] <= q0
 #pragma unroll
-    for (int step = NT / 2; step >= 1; step >>= 1)
-        if (u + step < nu && sh.upre[u + step] <= q0) u += step;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int x = q0 + j;
+    for (int j = 0; j < PER; ++j)
         k[j] = MKey{~0ull, ~0ull, 0x7FFFFFFF};  // beyond the segment: sorts last, dropped
-        if (x < q1) {
-            while (sh.upre[u + 1] <= x) ++u;  // skip ended and empty units (x < upre[nu])
-            const int64_t src = s0 + (int64_t)u * L.unit_stride + (x - sh.upre[u]);
-            k[j] = MKey{dbits(buf.T[src]), dbits(buf.E[src]), buf.I[src]};
-        }
-    }
+    points(q0, q1, k);
 #pragma unroll
     for (int w = 2; w <= PER; w <<= 1)
 #pragma unroll
@@ -441,17 +460,34 @@ __device__ __forceinline__ void merge_segment(int g, int n, const SegLayout &L,
     int count;
     int opos = block_exclusive<int, SumI32, NT / 64>(nkeep, 0, SumI32(), sh.sc32, &count);
     best = best0;
+    const int64_t d0 = place(count);
 #pragma unroll
     for (int j = 0; j < PER; ++j)
         if (e[j] < best) {
             const int q = q0 + j;
-            fin.T[s0 + opos] = bitsd(sh.T[cur][q]);
-            fin.E[s0 + opos] = bitsd(e[j]);
-            fin.I[s0 + opos] = sh.I[ord[q]];
+            if (d0 + opos < cap) {
+                oT[d0 + opos] = bitsd(sh.T[cur][q]);
+                oE[d0 + opos] = bitsd(e[j]);
+                oI[d0 + opos] = sh.I[ord[q]];
+            }
             ++opos;
             best = e[j];
         }
-    if (tid == 0) fcnt[g] = count;
+}
+
+// The union of segment g's n unit points into `fin` at the segment's start.
+template <int NT, int PER>
+__device__ __forceinline__ void merge_units(int g, int n, const SegLayout &L, const PointBufs &buf,
+                                            const PointBufs &fin, int32_t *fcnt,
+                                            MergeLds<NT, PER> &sh)
+{
+    const int64_t s0 = L.seg_off[g];
+    const UnitPoints<NT, PER> points{sh, buf, s0, L.unit_stride,
+                                     (int)(L.unit_base[g + 1] - L.unit_base[g])};
+    merge_segment(n, points, sh, fin.T, fin.E, fin.I, INT64_MAX, [&](int count) {
+        if (threadIdx.x == 0) fcnt[g] = count;
+        return s0;
+    });
 }
 
 // Stage 1: a block per segment.  lists[0] counts the segments passed on (zero on
@@ -464,7 +500,7 @@ finalize_small_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs
     const int g = blockIdx.x;
     if (g == 0 && threadIdx.x == 0) lists[1] = 0;
     int n;
-    if (merge_prefix(g, L, ucnt, sh, n)) merge_segment(g, n, L, buf, fin, fcnt, sh);
+    if (merge_prefix(g, L, ucnt, sh, n)) merge_units(g, n, L, buf, fin, fcnt, sh);
     else if (threadIdx.x == 0) lists[2 + atomicAdd(&lists[0], 1)] = g;
 }
 
@@ -479,19 +515,19 @@ finalize_large_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs
     for (int i = blockIdx.x; i < cnt; i += gridDim.x) {
         const int g = lists[2 + i];
         int n;
-        if (merge_prefix(g, L, ucnt, sh, n)) merge_segment(g, n, L, buf, fin, fcnt, sh);
+        if (merge_prefix(g, L, ucnt, sh, n)) merge_units(g, n, L, buf, fin, fcnt, sh);
         else if (threadIdx.x == 0) lists[2 + L.n_seg + atomicAdd(&lists[1], 1)] = g;
         __syncthreads();  // LDS reuse by the next segment
     }
 }
 
 // Stage 3, the segments on the second list: one block per segment (blocks loop over
-// the list).  The union is sorted in LDS when it fits; otherwise it is cut into
+// the list), returning the frontier's size.  The union is sorted in LDS when it fits; otherwise it is cut into
 // LDS-sized chunks whose frontiers are merged pairwise in device memory.
-__device__ void finalize_block_segment(int g, const SegLayout &L, const PointBufs &buf,
-                                       const int32_t *ucnt, const PointBufs &fin,
-                                       int32_t *fcnt, int32_t *runcnt, uint8_t *flags,
-                                       FinLds &sh, int32_t *sc)
+template <int NT>
+__device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs &buf,
+                                      const int32_t *ucnt, const PointBufs &fin, int32_t *runcnt,
+                                      uint8_t *flags, FinLds &sh, int32_t *sc)
 {
     const int64_t s0 = L.seg_off[g];
     const int64_t u0 = L.unit_base[g];
@@ -499,11 +535,11 @@ __device__ void finalize_block_segment(int g, const SegLayout &L, const PointBuf
     // unit sizes and their running offsets
     int64_t total = 0;
     const bool small_units = nu <= KR_FIN_UNITS;
-    for (int c0 = 0; c0 < nu; c0 += KR_BLOCK) {
+    for (int c0 = 0; c0 < nu; c0 += NT) {
         const int k = c0 + threadIdx.x;
         const int n = k < nu ? ucnt[u0 + k] : 0;
         int tot;
-        const int ex = block_exclusive(n, 0, SumI32(), sc, &tot);
+        const int ex = block_exclusive<int, SumI32, NT / 64>(n, 0, SumI32(), sc, &tot);
         if (small_units && k < nu) sh.upre[k] = (int)total + ex;
         total += tot;
     }
@@ -511,7 +547,7 @@ __device__ void finalize_block_segment(int g, const SegLayout &L, const PointBuf
     __syncthreads();
     if (small_units && total <= KR_FIN_CAP) {
         const int n = (int)total;
-        for (int x = threadIdx.x; x < n; x += KR_BLOCK) {
+        for (int x = threadIdx.x; x < n; x += NT) {
             int lo = 0, hi = nu - 1;  // unit holding element x
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
@@ -524,10 +560,10 @@ __device__ void finalize_block_segment(int g, const SegLayout &L, const PointBuf
             sh.sI[x] = buf.I[src];
         }
         __syncthreads();
-        lds_sort_keys(sh.sT, sh.sE, sh.sI, n);
-        const int cnt = lds_frontier_scan(sh.sT, sh.sE, sh.sI, n, fin.T + s0, fin.E + s0, fin.I + s0);
-        if (threadIdx.x == 0) fcnt[g] = cnt;
-        return;
+        lds_sort_keys<NT>(sh.sT, sh.sE, sh.sI, n);
+        const int cnt = lds_frontier_scan<NT>(sh.sT, sh.sE, sh.sI, n, fin.T + s0, fin.E + s0,
+                                              fin.I + s0);
+        return cnt;
     }
     // Large union: gather contiguously into fin, reduce LDS-sized chunks in place,
     // then merge the chunk staircases pairwise (fin <-> buf).
@@ -535,7 +571,7 @@ __device__ void finalize_block_segment(int g, const SegLayout &L, const PointBuf
     for (int k = 0; k < nu; ++k) {
         const int n = ld_l2(ucnt + u0 + k);
         const int64_t src = s0 + (int64_t)k * L.unit_stride;
-        for (int x = threadIdx.x; x < n; x += KR_BLOCK) {
+        for (int x = threadIdx.x; x < n; x += NT) {
             fin.T[s0 + pre + x] = buf.T[src + x];
             fin.E[s0 + pre + x] = buf.E[src + x];
             fin.I[s0 + pre + x] = buf.I[src + x];
@@ -548,14 +584,14 @@ __device__ void finalize_block_segment(int g, const SegLayout &L, const PointBuf
     for (int c = 0; c < nchunks; ++c) {
         const int64_t c0 = (int64_t)c * KR_FIN_CAP;
         const int n = (int)min((int64_t)KR_FIN_CAP, total - c0);
-        for (int x = threadIdx.x; x < n; x += KR_BLOCK) {
+        for (int x = threadIdx.x; x < n; x += NT) {
             sh.sT[x] = dbits(ld_l2(fin.T + s0 + c0 + x));
             sh.sE[x] = dbits(ld_l2(fin.E + s0 + c0 + x));
             sh.sI[x] = ld_l2(fin.I + s0 + c0 + x);
         }
         __syncthreads();
-        lds_sort_keys(sh.sT, sh.sE, sh.sI, n);
-        const int cnt = lds_frontier_scan(sh.sT, sh.sE, sh.sI, n, fin.T + s0 + c0, fin.E + s0 + c0,
+        lds_sort_keys<NT>(sh.sT, sh.sE, sh.sI, n);
+        const int cnt = lds_frontier_scan<NT>(sh.sT, sh.sE, sh.sI, n, fin.T + s0 + c0, fin.E + s0 + c0,
                                           fin.I + s0 + c0);
         if (threadIdx.x == 0) rc[c] = cnt;
         __syncthreads();
@@ -568,9 +604,9 @@ __device__ void finalize_block_segment(int g, const SegLayout &L, const PointBuf
             int merged;
             if (r + span < nchunks) {
                 const int64_t sb = s0 + (int64_t)(r + span) * KR_FIN_CAP;
-                merged = merge_pair(cur, other, flags, sa, na, sb, ld_l2(rc + r + span));
+                merged = merge_pair<NT>(cur, other, flags, sa, na, sb, ld_l2(rc + r + span));
             } else {
-                for (int x = threadIdx.x; x < na; x += KR_BLOCK) {
+                for (int x = threadIdx.x; x < na; x += NT) {
                     other.T[sa + x] = ld_l2(cur.T + sa + x);
                     other.E[sa + x] = ld_l2(cur.E + sa + x);
                     other.I[sa + x] = ld_l2(cur.I + sa + x);
@@ -587,13 +623,13 @@ __device__ void finalize_block_segment(int g, const SegLayout &L, const PointBuf
     }
     const int n = nchunks > 0 ? ld_l2(rc) : 0;
     if (cur.T != fin.T) {
-        for (int x = threadIdx.x; x < n; x += KR_BLOCK) {
+        for (int x = threadIdx.x; x < n; x += NT) {
             fin.T[s0 + x] = ld_l2(cur.T + s0 + x);
             fin.E[s0 + x] = ld_l2(cur.E + s0 + x);
             fin.I[s0 + x] = ld_l2(cur.I + s0 + x);
         }
     }
-    if (threadIdx.x == 0) fcnt[g] = n;
+    return n;
 }
 
 __global__ void __launch_bounds__(KR_BLOCK)
@@ -604,24 +640,127 @@ finalize_block_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs
     __shared__ int32_t sc[KR_WAVES];
     const int cnt = lists[1];
     for (int i = blockIdx.x; i < cnt; i += gridDim.x) {
-        finalize_block_segment(lists[2 + L.n_seg + i], L, buf, ucnt, fin, fcnt, runcnt, flags,
-                               sh, sc);
+        const int g = lists[2 + L.n_seg + i];
+        const int n = finalize_block_segment<KR_BLOCK>(g, L, buf, ucnt, fin, runcnt, flags, sh, sc);
+        if (threadIdx.x == 0) fcnt[g] = n;
         __syncthreads();  // LDS reuse by the next segment
     }
 }
 
-hipError_t launch_finalize(const SegLayout &L, const PointBufs &buf, const int32_t *ucnt,
-                           const PointBufs &fin, int32_t *fcnt, int32_t *runcnt, uint8_t *flags,
-                           int32_t *lists, hipStream_t st)
+// ----------------------------------------------------------------------------
+// All of the merge in one launch, for up to KR_FUSED_SEGS segments (one block of 1,024
+// threads each, which then fit on the chip together): a block merges its segment in LDS, or
+// in chunks when it is larger, publishes its count, and writes the frontier to its final
+// place as soon as the counts before it are known.  Blocks take their segments by ticket, so
+// a block waits only for segments of blocks that started before it.  Four launches of which
+// most blocks do nothing cost more than the merge itself where segments are few (4 to 256
+// partitions; the 1,518 configurations of a microbatch: 193 us a call, 126 us so).
+// RAW: the points come straight from (T, E), with no unit frontiers before (all segments
+// together hold at most the LDS capacity, so any of them fits).
+#define KR_FUSED_SEGS 256
+constexpr int kFusedCap = KR_FM_LARGE_NT * KR_FM_LARGE_PER;
+
+template <bool RAW>
+__global__ void __launch_bounds__(KR_FM_LARGE_NT)
+finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayout L,
+                      PointBufs buf, const int32_t *ucnt, PointBufs fin, int32_t *fcnt,
+                      int32_t *runcnt, uint8_t *flags, int32_t *lists, FrontierOut o,
+                      int32_t *status)
 {
-    if (L.n_seg == 0) return hipSuccess;
-    const dim3 loop_grid(min(L.n_seg, 256));
-    hipLaunchKernelGGL(finalize_small_kernel, dim3(L.n_seg), dim3(KR_FM_SMALL_NT), 0, st, L, buf,
-                       ucnt, fin, fcnt, lists);
-    hipLaunchKernelGGL(finalize_large_kernel, loop_grid, dim3(KR_FM_LARGE_NT), 0, st, L, buf,
-                       ucnt, fin, fcnt, lists);
-    hipLaunchKernelGGL(finalize_block_kernel, loop_grid, dim3(KR_BLOCK), 0, st, L, buf, ucnt,
-                       fin, fcnt, runcnt, flags, lists);
+    constexpr int NT = KR_FM_LARGE_NT, PER = KR_FM_LARGE_PER;
+    union Lds {
+        MergeLds<NT, PER> merge;
+        FinLds fin;
+        __device__ Lds() {}
+    };
+    __shared__ Lds sh;
+    __shared__ int32_t s_seg;
+    __shared__ int32_t sc32[NT / 64];
+    __shared__ int64_t sc64[NT / 64];
+    const int tid = threadIdx.x;
+    int g = 0;
+    if (L.n_seg > 1) {
+        if (tid == 0) s_seg = atomicAdd(&lists[0], 1);
+        __syncthreads();
+        g = s_seg;
+    }
+    // the first output element of segment g, which holds `count` points
+    auto place = [&](int count) -> int64_t {
+        int64_t d0 = 0;
+        if (L.n_seg > 1) {
+            static_assert(KR_FUSED_SEGS <= NT, "a thread per earlier segment");
+            if (tid == 0)
+                __hip_atomic_store(fcnt + g, count + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            int64_t before = 0;
+            if (tid < g) {
+                int32_t c;
+                while ((c = ld_l2(fcnt + tid)) == 0) __builtin_amdgcn_s_sleep(1);
+                before = c - 1;
+            }
+            d0 = block_reduce<int64_t, SumI64, NT / 64>(before, (int64_t)0, SumI64(), sc64);
+        }
+        if (tid == 0) {
+            o.off[g] = d0;
+            if (g == L.n_seg - 1) o.off[L.n_seg] = d0 + count;
+        }
+        return d0;
+    };
+    if (RAW) {
+        const int64_t s0 = L.seg_off[g];
+        const int n = (int)max((int64_t)0, min(L.seg_off[g + 1] - s0, n_total - s0));
+        uint32_t worst = 0;
+        auto points = [&](int q0, int q1, MKey (&k)[PER]) {
+#pragma unroll
+            for (int j = 0; j < PER; ++j)
+                if (q0 + j < q1) {
+                    // + 0.0 maps -0.0 to +0.0, so that the bit patterns order like the values
+                    const double t = T[s0 + q0 + j] + 0.0, e = E[s0 + q0 + j] + 0.0;
+                    worst = max(worst, max(raw_hi(t), raw_hi(e)));
+                    k[j] = MKey{dbits(t), dbits(e), q0 + j};
+                }
+        };
+        merge_segment(n, points, sh.merge, o.T, o.E, o.idx, o.cap, place);
+        if (status) {
+            if (L.n_seg > 1) {
+                report_values(status, worst >= KR_BAD_HI);  // KR_OK before the launch
+            } else {
+                const int bad = __syncthreads_or(worst >= KR_BAD_HI);
+                if (tid == 0) *status = bad ? KR_ENONFINITE : KR_OK;
+            }
+        }
+        return;
+    }
+    int n;
+    if (merge_prefix(g, L, ucnt, sh.merge, n)) {
+        const UnitPoints<NT, PER> points{sh.merge, buf, L.seg_off[g], L.unit_stride,
+                                         (int)(L.unit_base[g + 1] - L.unit_base[g])};
+        merge_segment(n, points, sh.merge, o.T, o.E, o.idx, o.cap, place);
+        return;
+    }
+    __syncthreads();
+    n = finalize_block_segment<NT>(g, L, buf, ucnt, fin, runcnt, flags, sh.fin, sc32);
+    __syncthreads();  // the block's stores to fin are read back below
+    const int64_t d0 = place(n), src0 = L.seg_off[g];
+    for (int64_t x = tid; x < n && d0 + x < o.cap; x += NT) {
+        o.idx[d0 + x] = ld_l2(fin.I + src0 + x);
+        o.T[d0 + x] = ld_l2(fin.T + src0 + x);
+        o.E[d0 + x] = ld_l2(fin.E + src0 + x);
+    }
+}
+
+bool pareto_raw(int64_t n_total, int n_seg)
+{
+    return n_seg >= 1 && n_seg <= KR_FUSED_SEGS && n_total <= kFusedCap;
+}
+
+hipError_t launch_pareto_raw(const double *T, const double *E, int64_t n_total, const SegLayout &L,
+                             int32_t *fcnt, int32_t *lists, const FrontierOut &o, int32_t *status,
+                             hipStream_t st)
+{
+    const PointBufs none{nullptr, nullptr, nullptr};
+    hipLaunchKernelGGL(finalize_fused_kernel<true>, dim3(L.n_seg), dim3(KR_FM_LARGE_NT), 0, st, T,
+                       E, n_total, L, none, (const int32_t *)nullptr, none, fcnt,
+                       (int32_t *)nullptr, (uint8_t *)nullptr, lists, o, status);
     return hipGetLastError();
 }
 
@@ -686,7 +825,22 @@ copy_out_scan_kernel(SegLayout L, PointBufs fin, const int32_t *fcnt, int64_t *o
     }
 }
 
-hipError_t launch_output(const SegLayout &L, const PointBufs &fin, const int32_t *fcnt,
+static hipError_t launch_finalize(const SegLayout &L, const PointBufs &buf, const int32_t *ucnt,
+                           const PointBufs &fin, int32_t *fcnt, int32_t *runcnt, uint8_t *flags,
+                           int32_t *lists, hipStream_t st)
+{
+    if (L.n_seg == 0) return hipSuccess;
+    const dim3 loop_grid(min(L.n_seg, 256));
+    hipLaunchKernelGGL(finalize_small_kernel, dim3(L.n_seg), dim3(KR_FM_SMALL_NT), 0, st, L, buf,
+                       ucnt, fin, fcnt, lists);
+    hipLaunchKernelGGL(finalize_large_kernel, loop_grid, dim3(KR_FM_LARGE_NT), 0, st, L, buf,
+                       ucnt, fin, fcnt, lists);
+    hipLaunchKernelGGL(finalize_block_kernel, loop_grid, dim3(KR_BLOCK), 0, st, L, buf, ucnt,
+                       fin, fcnt, runcnt, flags, lists);
+    return hipGetLastError();
+}
+
+static hipError_t launch_output(const SegLayout &L, const PointBufs &fin, const int32_t *fcnt,
                          int64_t cap, int64_t *out_off, int32_t *out_idx, double *out_T,
                          double *out_E, hipStream_t st)
 {
@@ -701,6 +855,21 @@ hipError_t launch_output(const SegLayout &L, const PointBufs &fin, const int32_t
     hipLaunchKernelGGL(copy_out_kernel, dim3(L.n_seg), dim3(KR_BLOCK), 0, st, L, fin, out_off, cap,
                        out_idx, out_T, out_E);
     return hipGetLastError();
+}
+
+hipError_t launch_merge(const SegLayout &L, const PointBufs &buf, const int32_t *ucnt,
+                        const PointBufs &fin, int32_t *fcnt, int32_t *runcnt, uint8_t *flags,
+                        int32_t *lists, const FrontierOut &o, hipStream_t st)
+{
+    if (L.n_seg >= 1 && L.n_seg <= KR_FUSED_SEGS) {
+        hipLaunchKernelGGL(finalize_fused_kernel<false>, dim3(L.n_seg), dim3(KR_FM_LARGE_NT), 0, st,
+                           (const double *)nullptr, (const double *)nullptr, (int64_t)0, L, buf,
+                           ucnt, fin, fcnt, runcnt, flags, lists, o, (int32_t *)nullptr);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_finalize(L, buf, ucnt, fin, fcnt, runcnt, flags, lists, st);
+    if (e != hipSuccess) return e;
+    return launch_output(L, fin, fcnt, o.cap, o.off, o.idx, o.T, o.E, st);
 }
 
 }  // namespace kr
