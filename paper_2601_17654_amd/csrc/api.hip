@@ -501,24 +501,17 @@ kr_status kr_extract_schedule(int32_t n_parts, int32_t n_bins, const int32_t *bp
 
 // Workspace of the microbatch frontier; every pointer is null when base is null.
 struct MbWs {
-    int64_t *seg, *front_off;
-    double *slot_T, *slot_E, *front_T, *front_E;
+    int64_t *front_off;
     int32_t *slot_choice, *front_idx;
     MbGridWs g;
-    void *pws;
-    size_t pws_bytes;
+    FilterWs f;
 };
 
 static MbWs carve_mb(Carve &c, int K, int F, int B)
 {
     MbWs w;
     const int64_t S = (int64_t)F * B;
-    w.seg = c.take<int64_t>(2);
     w.front_off = c.take<int64_t>(2);
-    w.slot_T = c.take<double>(S);
-    w.slot_E = c.take<double>(S);
-    w.front_T = c.take<double>(S);
-    w.front_E = c.take<double>(S);
     w.slot_choice = c.take<int32_t>((size_t)S * K);
     w.front_idx = c.take<int32_t>(S);
     w.g.ob2 = c.take<int32_t>(S);
@@ -527,8 +520,11 @@ static MbWs carve_mb(Carve &c, int K, int F, int B)
     w.g.F = c.take<double>(2 * S);
     w.g.bp = c.take<int32_t>((size_t)S * K);
     w.g.stair = c.take<int32_t>(S);
-    w.pws_bytes = kr_pareto_filter_workspace(S, 1);
-    w.pws = c.take<char>(w.pws_bytes);
+    w.f = carve_filter(c, S, 1, F, true);
+    w.g.seg_off = w.f.seg_off;
+    w.g.unit_base = w.f.unit_base;
+    w.g.buf = w.f.buf[0];
+    w.g.ucnt = w.f.ucnt;
     return w;
 }
 
@@ -585,18 +581,17 @@ kr_status kr_microbatch_frontier(int32_t n_types, int32_t n_freq, const int64_t 
     hipStream_t st = (hipStream_t)stream;
     Carve c(ws);
     MbWs w = carve_mb(c, n_types, n_freq, n_bins);
-    a.slot_T = w.slot_T;
-    a.slot_E = w.slot_E;
+    a.slot_T = a.slot_E = nullptr;
     a.slot_choice = w.slot_choice;
     if (launch_mb_grid(a, w.g, st) != hipSuccess) return KR_EHIP;
-    const int64_t S = (int64_t)n_freq * n_bins;
-    if (launch_mb_seg(w.seg, S, st) != hipSuccess) return KR_EHIP;
-    const kr_status rc = kr_pareto_filter(S, w.slot_T, w.slot_E, w.seg, 1, S, w.front_off,
-                                          w.front_idx, w.front_T, w.front_E, nullptr, w.pws,
-                                          w.pws_bytes, stream);
+    const SegLayout L{w.f.seg_off, w.f.unit_base, 1, n_bins};
+    // an output never holds more points than there are slots
+    const int64_t most = std::min(cap, (int64_t)n_freq * n_bins);
+    const FrontierOut o{most, w.front_off, w.front_idx, out_T, out_E};
+    const kr_status rc = finish_segments(L, w.f, o, st);
     if (rc != KR_OK) return rc;
-    return launch_mb_gather(a, w.front_off, w.front_idx, cap, out_T, out_E, out_f, out_choice,
-                            n_out, st) == hipSuccess
+    return launch_mb_gather(a, w.front_off, w.front_idx, cap, out_f, out_choice, n_out, st) ==
+                   hipSuccess
                ? KR_OK
                : KR_EHIP;
 }
@@ -605,7 +600,7 @@ kr_status kr_microbatch_frontier(int32_t n_types, int32_t n_freq, const int64_t 
 struct MbEnumWs {
     int64_t *base, *seg, *front_off;
     int32_t *status, *front_idx;
-    double *slot_T, *slot_E, *front_T, *front_E;
+    double *slot_T, *slot_E;
     void *pws;
     size_t pws_bytes;
 };
@@ -620,8 +615,6 @@ static MbEnumWs carve_mb_enum(Carve &c, int F, int64_t slots)
     w.front_idx = c.take<int32_t>(slots);
     w.slot_T = c.take<double>(slots);
     w.slot_E = c.take<double>(slots);
-    w.front_T = c.take<double>(slots);
-    w.front_E = c.take<double>(slots);
     w.pws_bytes = kr_pareto_filter_workspace(slots, 1);
     w.pws = c.take<char>(w.pws_bytes);
     return w;
@@ -682,17 +675,13 @@ kr_status kr_microbatch_enumerate(int32_t n_types, int32_t n_freq, const int64_t
     a.slot_T = w.slot_T;
     a.slot_E = w.slot_E;
     a.slot_choice = nullptr;
-    if (launch_mb_enum(a, w.base, n_configs, w.status, st) != hipSuccess) return KR_EHIP;
-    if (launch_mb_seg(w.seg, n_configs, st) != hipSuccess) return KR_EHIP;
-    const kr_status rc = kr_pareto_filter(n_configs, w.slot_T, w.slot_E, w.seg, 1, n_configs,
-                                          w.front_off, w.front_idx, w.front_T, w.front_E, nullptr,
-                                          w.pws, w.pws_bytes, stream);
+    if (launch_mb_enum(a, w.base, w.seg, n_configs, w.status, st) != hipSuccess) return KR_EHIP;
+    const kr_status rc =
+        kr_pareto_filter(n_configs, w.slot_T, w.slot_E, w.seg, 1, std::min(cap, n_configs),
+                         w.front_off, w.front_idx, out_T, out_E, nullptr, w.pws, w.pws_bytes, stream);
     if (rc != KR_OK) return rc;
-    if (launch_mb_enum_gather(a, w.base, w.status, w.front_off, w.front_idx, cap, out_T, out_E,
-                              out_f, out_choice, n_out, n_configs, st) != hipSuccess)
-        return KR_EHIP;
-    return hipMemcpyAsync(status_out, w.status, sizeof(int32_t), hipMemcpyDeviceToDevice, st) ==
-                   hipSuccess
+    return launch_mb_enum_gather(a, w.base, w.status, w.front_off, w.front_idx, cap, out_f,
+                                 out_choice, n_out, status_out, n_configs, st) == hipSuccess
                ? KR_OK
                : KR_EHIP;
 }

@@ -184,30 +184,34 @@ struct MbArgs {
     int32_t used[KR_MB_MAX_TYPES];   // used types, in type order
     int32_t count[KR_MB_MAX_TYPES];  // their repeat counts
     uint8_t seq_u[KR_MB_MAX_SEQ];    // used-type index of each partition
-    double *slot_T, *slot_E;         // [F * B]
-    int32_t *slot_choice;            // [F * B][K]
+    double *slot_T, *slot_E;         // enumeration: [slots]
+    int32_t *slot_choice;            // grid: [F * B][K]
 };
-// Per-frequency workspace of the grid microbatch frontier (region f of each array is
-// frequency f's): the occupied offsets of the type being binned [B] (offset, least
-// energy, point), the composite arrays of two steps [2][B], the back-pointers [K][B] and
-// the staircase bins [B].
+// Workspace of the grid microbatch frontier.  Region f of an array is frequency f's: the
+// occupied offsets of the type being binned [B] (offset, least energy, point; those past the
+// on-chip list), the composite arrays of two steps [2][B] (when they do not fit on chip), the
+// back-pointers [K][B] and the staircase bins [B].  The configurations found are the units of
+// one segment (layout, slots and counts).
 struct MbGridWs {
     int32_t *ob2, *oarg;
     double *oe, *F;
     int32_t *bp, *stair;
+    int64_t *seg_off, *unit_base;  // [2]
+    PointBufs buf;                 // [F * B]
+    int32_t *ucnt;                 // [F]
 };
 hipError_t launch_mb_grid(const MbArgs &a, const MbGridWs &w, hipStream_t st);
-hipError_t launch_mb_seg(int64_t *seg, int64_t n, hipStream_t st);
 hipError_t launch_mb_gather(const MbArgs &a, const int64_t *front_off, const int32_t *front_idx,
-                            int64_t cap, double *out_T, double *out_E, int32_t *out_f,
-                            int32_t *out_choice, int64_t *n_out, hipStream_t st);
-// Enumeration: base [F + 1] configuration totals, status [1]; slot_T / slot_E [slots].
-hipError_t launch_mb_enum(const MbArgs &a, int64_t *base, int64_t slots, int32_t *status,
-                          hipStream_t st);
+                            int64_t cap, int32_t *out_f, int32_t *out_choice, int64_t *n_out,
+                            hipStream_t st);
+// Enumeration: base [F + 1] configuration totals, seg [2] the segment of all slots, status
+// [1]; slot_T / slot_E [slots].
+hipError_t launch_mb_enum(const MbArgs &a, int64_t *base, int64_t *seg, int64_t slots,
+                          int32_t *status, hipStream_t st);
 hipError_t launch_mb_enum_gather(const MbArgs &a, const int64_t *base, const int32_t *status,
                                  const int64_t *front_off, const int32_t *front_idx, int64_t cap,
-                                 double *out_T, double *out_E, int32_t *out_f, int32_t *out_choice,
-                                 int64_t *n_out, int64_t slots, hipStream_t st);
+                                 int32_t *out_f, int32_t *out_choice, int64_t *n_out,
+                                 int32_t *status_out, int64_t slots, hipStream_t st);
 
 // mbo.hip: scores and batch selection of the Bayesian optimisation (Section 4.3,
 // Algorithm 1).
