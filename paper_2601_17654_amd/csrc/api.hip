@@ -123,9 +123,16 @@ bool pair_plan(EvalArgs *a)
     a->q_f = (int)(a->q_ab + 2 * (a->N + 1) * S1);  // {A, B} records
     a->q_c = (int)(a->q_f + 6 * (int64_t)a->n_pos * a->S);  // 6-double records
     constexpr int NW = KR_PAIR_WAVES;
-    a->q_sc = a->q_c + NW * 6 * 64;                     // one set per wave
-    const int64_t lds = a->q_sc + NW * (64 + 64 + 32);  // scratch T, E, indices per wave
-    if ((size_t)lds * 8 > kLdsBudget) return false;
+    const int64_t pairs = (int64_t)a->n_pos * a->S;
+    // one set per wave, and room for the pairs' own parts before that
+    a->q_sc = a->q_c + (int)std::max<int64_t>(NW * 6 * 64, 2 * pairs);
+    // scratch T, E, indices per wave; room for two 16-bit champions per position before that
+    a->q_l = a->q_sc + (int)std::max<int64_t>(NW * (64 + 64 + 32), (a->n_pos + 1) / 2);
+    const int64_t lds = a->q_l + 2 * a->S + (pairs + 3) / 4;
+    // taken where everything but the list and the parts' overhang fits the budget (those are
+    // a few KB, so that up to 70 KB are asked for)
+    const int64_t base = a->q_c + NW * 6 * 64 + NW * (64 + 64 + 32);
+    if ((size_t)base * 8 > kLdsBudget) return false;
     a->pair = 1;
     a->lds_doubles = (int)lds;
     // each wave's slab-end reduction sorts in its share of the second-phase tables (20

@@ -18,6 +18,20 @@
 //  - otherwise the second comm kernel starts as soon as the first ends and continues
 //    the first phase's progress: that phase depends on (p1, s1, s2), and each lane
 //    forms it once per p1.
+// Most candidates need no evaluation at all:
+//  - every second launch position that compute has passed by the time the first comm kernel
+//    ends (p2 <= j1) gives the same walk, so of those only p2 = p1, the first in candidate
+//    order, can be kept;
+//  - a later one (p2 > j1) adds its own part, which depends on (p2, s2) only: X = A0[p2] +
+//    tc2 + rest to the time and Z = static power * X + its energies to the energy.  A pair
+//    q = (p2, s2) whose X and Z both exceed those of another pair with the same or a later
+//    position is worse in every candidate that could hold it (the other one is available
+//    there too), and is dropped for the slab.  X and Z must differ by more than the roundings
+//    of a candidate's sums can undo (KR_PAIR_MARGIN), so what is dropped is strictly worse
+//    in the rounded results as well, and the frontier is the same, point for point.
+// Of the two-comm workload's 264 pairs per slab 9 are left on average, and a launch position
+// and SM choice take 8 + 9 evaluations instead of 264 to 8 (kernel 931 us with all of them,
+// 492 us without).
 // A phase is kept as the values it adds to the energy sum and to the time, in the
 // order the walk adds them.  A candidate applies them to its own sums in that order,
 // so every candidate gets the roundings of the plain walk, operation for operation.
@@ -235,16 +249,39 @@ __device__ __forceinline__ void copy_to_lds_nw(const double *g, double *l, int n
     }
 }
 
+// Roundings: a time is at most 5 operations on values up to Tm from its parts, X 2; an
+// energy 9 and 5 of the time's (times static power) on values up to Em, Z 8 and 2.  With
+// u = 2^-53 two candidates keep the order of their parts when those differ by 14 u Tm and
+// 48 u Em; the margins are twice that and more.
+#define KR_PAIR_MARGIN_T (32 * 0x1p-53)
+#define KR_PAIR_MARGIN_E (128 * 0x1p-53)
+
+// Pair (p2, s2)'s own part of the time and energy of the candidates that start it fresh.
+struct alignas(16) PairPart {
+    double x, z;
+};
+
+// Wave maximum of two non-NaN doubles (every lane active; uniform).
+__device__ __forceinline__ void wave_max2_f64(double &x, double &y)
+{
+    x = -x;
+    y = -y;
+    wave_min2_f64(x, y);
+    x = -x;
+    y = -y;
+}
+
 // Block (p, b): NW waves sharing the slabs of partition p, frequencies [b*fb,
 // min(F, (b+1)*fb)), one slab at a time.  LDS (in doubles): t slab [N][S1] at 0, pw slab
 // at q_pw, running sums {A, B} [N + 1][S1] at q_ab (column 0 the all-SM state), the
 // fresh second-phase table [n_pos][S] at q_f, each wave's continuing second phases [64]
-// at q_c, each wave's filter scratch at q_sc.  Launch positions p1 go to the waves in
-// snake order (0, 1, .., NW - 1, NW - 1, .., 0, 0, 1, ..), which evens out the pairs
-// each wave takes; a wave is a unit of its own (slot and count), so waves never share
-// output.
-// Round r of a chunk evaluates pair (p1, c0 + r) for every lane; pairs past the last
-// position are clamped for the loads and give +inf.  Each chunk's frontier goes to the
+// at q_c (the pairs' own parts before those), each wave's filter scratch at q_sc (the
+// positions' champions before that), the list of the pairs kept at q_l, after the second
+// comm kernel's times and energies [2][S].  Launch positions p1 go to the waves in
+// snake order (0, 1, .., NW - 1, NW - 1, .., 0, 0, 1, ..); a wave is a unit of its own (slot
+// and count), so waves never share output.
+// Lane (s1, s2) evaluates, for each p1, the candidate that continues with s2, then every
+// S-th of the kept pairs from the s2-th on.  Each chunk's frontier goes to the
 // wave's slot; at the end of a slab those points (usually many times the slab's own
 // frontier) are read back into the second-phase tables, idle by then, sorted, and
 // replaced in place by their frontier, when they fit there.  SC > 0 fixes the number of
@@ -277,6 +314,12 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
     int count = 0;
     uint32_t worst = 0;  // largest high word read (input check)
     const double p_static = a.p_static;
+    __shared__ int32_t s_kept;  // pairs kept
+    PairPart *const part = (PairPart *)(lds + a.q_c);        // [np][S]
+    int16_t *const champ = (int16_t *)(lds + a.q_sc);        // [np][2]
+    double *const ltc = lds + a.q_l, *const lct = ltc + S;   // [S] each
+    int16_t *const list = (int16_t *)(lds + a.q_l + 2 * S);  // [np * S]
+    const int npS = np * S;
     // sort room of the slab-end reduction: this wave's share of the fresh and continuing
     // tables
     const int scap = a.pair_scap;
@@ -332,11 +375,106 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
         __syncthreads();
         // Second comm phases that start fresh at kernel q.  Row q = N (a comm kernel
         // launched after the last compute kernel) adds nothing: all +0.
-        if (g < G)
-            for (int q = g; q < np; q += G)
-                Fr[q * S + sF] = q < N ? pair_phase(Lt, Lp, AB, S1, N, sF + 1, q, 1.0, tcF)
-                                       : PairRec{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        if (g < G) {
+            const double ctF = cpw[S + sF] * tcF;
+            if (g == 0) {
+                ltc[sF] = tcF;
+                lct[sF] = ctF;
+            }
+            for (int q = g; q < np; q += G) {
+                const PairRec o = q < N ? pair_phase(Lt, Lp, AB, S1, N, sF + 1, q, 1.0, tcF)
+                                        : PairRec{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+                const ColRec z = AB[q * S1];
+                const double x = (z.a + tcF) + o.el4;
+                Fr[q * S + sF] = o;
+                part[q * S + sF] = PairPart{
+                    x, (p_static * x + ((((z.b + o.eb) + o.ec) + o.a4) + o.b4)) + ctF};
+            }
+        }
+        // bounds of the slab's times and energies, for the margins (any wave's lanes cover
+        // every SM choice and state)
+        double mt1 = tc1, mt2 = tc2, mc = ct1 + ct2;
+        double mb = lane < S1 ? AB[N * S1 + lane].b : 0.0;
+        wave_max2_f64(mt1, mt2);
+        wave_max2_f64(mc, mb);
+        const ColRec zall = AB[N * S1];
+        const double Tm = 2.0 * zall.a + (mt1 + mt2), Em = p_static * Tm + (10.0 * mb + mc);
+        const double dT = KR_PAIR_MARGIN_T * Tm, dE = KR_PAIR_MARGIN_E * Em;
+        if (tid == 0) s_kept = 0;
         __syncthreads();
+        // Champions: per position the pair at it or later with the least Z + c X, for two
+        // weights c around the slab's mean power (a time-leaning and an energy-leaning one).
+        // Testing every pair against these two keeps 9 of 264, against all of them 7.
+        if (wave == 0) {
+            const double mean = zall.a > 0.0 ? p_static + zall.b / zall.a : p_static;
+            const double c0 = 0.25 * mean, c1 = 4.0 * mean;
+            double l0 = INFINITY, l1 = INFINITY;  // least of the later positions (uniform)
+            int a0 = 0, a1 = 0;
+            for (int base = (np - 1) / 64 * 64; base >= 0; base -= 64) {
+                double g0 = INFINITY, g1 = INFINITY;
+                int i0 = 0, i1 = 0;
+                if (base + lane < np)
+                    for (int c = 0; c < S; ++c) {
+                        const int q = (base + lane) * S + c;
+                        const PairPart y = part[q];
+                        const double v0 = y.z + c0 * y.x, v1 = y.z + c1 * y.x;
+                        i0 = v0 < g0 ? q : i0;
+                        g0 = v0 < g0 ? v0 : g0;
+                        i1 = v1 < g1 ? q : i1;
+                        g1 = v1 < g1 ? v1 : g1;
+                    }
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {  // least of lanes lane ..
+                    const double y0 = __shfl_down(g0, d, 64), y1 = __shfl_down(g1, d, 64);
+                    const int j0 = __shfl_down(i0, d, 64), j1 = __shfl_down(i1, d, 64);
+                    if (lane + d < 64 && y0 < g0) {
+                        g0 = y0;
+                        i0 = j0;
+                    }
+                    if (lane + d < 64 && y1 < g1) {
+                        g1 = y1;
+                        i1 = j1;
+                    }
+                }
+                if (l0 < g0) {
+                    g0 = l0;
+                    i0 = a0;
+                }
+                if (l1 < g1) {
+                    g1 = l1;
+                    i1 = a1;
+                }
+                if (base + lane < np) {
+                    champ[2 * (base + lane)] = (int16_t)i0;
+                    champ[2 * (base + lane) + 1] = (int16_t)i1;
+                }
+                l0 = bitsd(lane_u64(dbits(g0), 0));
+                l1 = bitsd(lane_u64(dbits(g1), 0));
+                a0 = lane_i32(i0, 0);
+                a1 = lane_i32(i1, 0);
+            }
+        }
+        __syncthreads();
+        for (int q0 = 64 * wave; q0 < npS; q0 += 64 * NW) {
+            const int q = q0 + lane;
+            bool keep = q < npS;
+            if (keep) {
+                const PairPart y = part[q];
+                const int p2 = q / S;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const PairPart b = part[champ[2 * p2 + h]];
+                    if (b.x + dT < y.x && b.z + dE < y.z) keep = false;
+                }
+            }
+            const uint64_t m = __ballot(keep);
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&s_kept, __popcll(m));
+            at = lane_i32(at, 0) + lane_rank(m);
+            if (keep) list[at] = (int16_t)q;
+        }
+        __syncthreads();
+        const int nk = s_kept;
 
         for (int p1 = 0; p1 < np; ++p1) {
             if (pair_owner(p1, NW) != wave) continue;
@@ -368,39 +506,58 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
             Cw[lane] = j1 < N ? pair_phase(Lt, Lp, AB, S1, N, s2 + 1, j1, w1, tc2)
                               : PairRec{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
             wave_lds_fence();
-            const int ppb = p1 * np - p1 * (p1 - 1) / 2 - p1;  // pair rank of (p1, p2): ppb + p2
-            for (int c0 = p1; c0 < np; c0 += R) {
+            // pair rank of (p1, p2): ppb + p2
+            const int ppb = p1 * np - p1 * (p1 - 1) / 2 - p1;
+            const int i1 = f * a.Cf + s1 * S;
+            // time and energy from a second phase: st2 its start, Ec the energy before it
+            auto finish = [&](const PairRec &q, double st2, double Ec, double tcs, double cts,
+                              double &T, double &E) {
+                Ec = Ec + q.ea;
+                Ec = Ec + q.eb;
+                Ec = Ec + q.ec;
+                Ec = Ec + q.a4;
+                Ec = Ec + q.b4;
+                T = (st2 + tcs) + q.el4;
+                E = p_static * T;
+                E = E + Ec;
+                E = E + ct1;
+                E = E + cts;
+            };
+            // chunks of R slots: the continuing candidate first, then rounds of kept pairs
+            for (int e0 = -S; e0 < nk; e0 += R * S) {
                 double vT[R], vE[R];
+                int32_t vI[R];
                 double tl = INFINITY, el = INFINITY;
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const int p2 = min(c0 + r, np - 1);
-                    const bool valid = live && c0 + r < np;
-                    const bool fresh = j1 < p2;
-                    const ColRec z2 = AB[p2 * S1];
-                    const PairRec q = *(fresh ? Fr + p2 * S + s2 : Cw + lane);
-                    const double EcF = Eca + (z2.b - zi2.b);
-                    const double stF = tau1 + (used2 + (z2.a - zi2.a));
-                    double Ec = fresh ? EcF : Ec1;
-                    const double st2 = fresh ? stF : tau1;
-                    Ec = Ec + q.ea;
-                    Ec = Ec + q.eb;
-                    Ec = Ec + q.ec;
-                    Ec = Ec + q.a4;
-                    Ec = Ec + q.b4;
-                    const double T = (st2 + tc2) + q.el4;
-                    double E = p_static * T;
-                    E = E + Ec;
-                    E = E + ct1;
-                    E = E + ct2;
-                    vT[r] = valid ? T : INFINITY;
-                    vE[r] = valid ? E : INFINITY;
+                    const int e = e0 + r * S;  // this round's first entry of the list
+                    vT[r] = INFINITY;
+                    vE[r] = INFINITY;
+                    vI[r] = 0;
+                    if (e >= nk) continue;  // uniform
+                    if (r == 0 && e < 0) {
+                        finish(Cw[lane], tau1, Ec1, tc2, ct2, vT[r], vE[r]);
+                        vI[r] = i1 + (ppb + p1) * SS + s2;
+                        vT[r] = live ? vT[r] : INFINITY;
+                        vE[r] = live ? vE[r] : INFINITY;
+                    } else {
+                        const bool in = live && e + s2 < nk;
+                        const int q = in ? list[e + s2] : 0;
+                        const int p2 = q / S, c = q - p2 * S;
+                        const ColRec z2 = AB[p2 * S1];
+                        const bool valid = in && j1 < p2;  // fresh: compute has not reached p2
+                        double T, E;
+                        finish(Fr[q], tau1 + (used2 + (z2.a - zi2.a)), Eca + (z2.b - zi2.b), ltc[c],
+                               lct[c], T, E);
+                        vI[r] = i1 + (ppb + p2) * SS + c;
+                        vT[r] = valid ? T : INFINITY;
+                        vE[r] = valid ? E : INFINITY;
+                    }
                     tl = vmin(tl, vT[r]);
                     el = vmin(el, vE[r]);
                 }
-                const int ibase = f * a.Cf + (ppb + c0) * SS + lane;
-                count += wave_frontier<R>(vT, vE, tl, el, ibase, SS, sc, oT + count, oE + count,
-                                          oI + count);
+                count += wave_frontier<R>(vT, vE, tl, el, [&](int r) { return vI[r]; }, sc,
+                                          oT + count, oE + count, oI + count);
             }
             wave_lds_fence();  // the continuing phase of this p1 is read
         }
@@ -432,13 +589,13 @@ hipError_t launch_eval_filter_pair(const EvalArgs &a, const UnitOut &o, hipStrea
     constexpr int NW = KR_PAIR_WAVES;
     const dim3 grid(a.P * a.nfb), block(64 * NW);
     if (a.dma16 && a.S == 8 && a.N == 48 && a.n_pos == 33)
-        hipLaunchKernelGGL((eval_filter_pair_kernel<8, 16, NW, 8, true>), grid, block, lds, st, a, o);
+        hipLaunchKernelGGL((eval_filter_pair_kernel<4, 16, NW, 8, true>), grid, block, lds, st, a, o);
     else if (a.dma16 && a.S == 8)
-        hipLaunchKernelGGL((eval_filter_pair_kernel<8, 16, NW, 8, false>), grid, block, lds, st, a, o);
+        hipLaunchKernelGGL((eval_filter_pair_kernel<4, 16, NW, 8, false>), grid, block, lds, st, a, o);
     else if (a.dma16)
-        hipLaunchKernelGGL((eval_filter_pair_kernel<8, 16, NW, 0, false>), grid, block, lds, st, a, o);
+        hipLaunchKernelGGL((eval_filter_pair_kernel<4, 16, NW, 0, false>), grid, block, lds, st, a, o);
     else
-        hipLaunchKernelGGL((eval_filter_pair_kernel<8, 4, NW, 0, false>), grid, block, lds, st, a, o);
+        hipLaunchKernelGGL((eval_filter_pair_kernel<4, 4, NW, 0, false>), grid, block, lds, st, a, o);
     return hipGetLastError();
 }
 

@@ -332,8 +332,8 @@ __global__ void __launch_bounds__(64) eval_filter_wave_kernel(EvalArgs a, UnitOu
                 pc_next = a.pc[pn * S + s];
             }
             const int ibase = f * a.Cf + c0 * S + s;
-            count += wave_frontier<R>(vT, vE, tl, el, ibase, S, sc, oT + count, oE + count,
-                                      oI + count);
+            count += wave_frontier<R>(vT, vE, tl, el, [&](int r) { return ibase + r * S; }, sc,
+                                      oT + count, oE + count, oI + count);
         }
     }
     if (lane == 0) o.cnt[blockIdx.x] = count;

@@ -50,9 +50,9 @@ struct EvalArgs {
     int fixed32;
     // one wave per slab (two comm kernels, at most 8 SM choices): LDS offsets (doubles)
     // of the power slab, the running sums, the fresh and continuing second-phase
-    // records and the filter scratch
+    // records, the filter scratch and the list of second-phase pairs kept
     int pair;
-    int q_pw, q_ab, q_f, q_c, q_sc;
+    int q_pw, q_ab, q_f, q_c, q_sc, q_l;
     int pair_scap;          // most chunk outputs of a slab a wave reduces to its frontier on chip
     // unit slots of the fused launch: points per partition segment, units per segment,
     // points per unit

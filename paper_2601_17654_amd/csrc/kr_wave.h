@@ -108,9 +108,9 @@ __device__ __forceinline__ void emit(const Key &k, int n, double *oT, double *oE
 
 // Least (T, E, index) candidate among those with pred(r) true.  Fast path when exactly
 // one candidate of the wave qualifies; otherwise a full lexicographic reduction.
-template <int R, typename Pred>
-__device__ __forceinline__ Key chunk_pick(const double (&vT)[R], const double (&vE)[R], int ibase,
-                                          int S, Pred pred)
+template <int R, typename Index, typename Pred>
+__device__ __forceinline__ Key chunk_pick(const double (&vT)[R], const double (&vE)[R],
+                                          const Index &index, Pred pred)
 {
     int cnt = 0;
     Key one = key_none();
@@ -121,7 +121,7 @@ __device__ __forceinline__ Key chunk_pick(const double (&vT)[R], const double (&
             cnt += __popcll(m);
             const int L = __ffsll((long long)m) - 1;
             one = Key{lane_u64(dbits(vT[r]), L), lane_u64(dbits(vE[r]), L),
-                      lane_i32(ibase, L) + r * S};
+                      lane_i32(index(r), L)};
         }
     }
     if (cnt == 1) return one;
@@ -129,7 +129,7 @@ __device__ __forceinline__ Key chunk_pick(const double (&vT)[R], const double (&
 #pragma unroll
     for (int r = 0; r < R; ++r)
         if (pred(r)) {
-            const Key c{dbits(vT[r]), dbits(vE[r]), ibase + r * S};
+            const Key c{dbits(vT[r]), dbits(vE[r]), index(r)};
             if (kless(c, loc)) loc = c;
         }
     return wave_min_key(loc);
@@ -143,8 +143,8 @@ struct Scratch {
 };
 
 // Frontier of the wave's chunk (invalid slots hold T = E = +inf; valid ones are
-// finite); tl, el are each lane's least T and E.  Candidate index of slot r of a lane
-// is ibase + r * S.  Writes the frontier in ascending T to o*[0 .. n) and returns n
+// finite); tl, el are each lane's least T and E.  index(r) is the candidate index of this
+// lane's slot r.  Writes the frontier in ascending T to o*[0 .. n) and returns n
 // (uniform).
 //
 // A (least in (T, E, index) order) and Z (least in (E, T, index) order) come from wave
@@ -153,22 +153,22 @@ struct Scratch {
 // gathered one candidate per lane and each keeps itself iff no other member precedes
 // it with energy at or below its own; kept points are placed by their rank in T.  A
 // box larger than the scratch takes repeated wave minima instead (same result).
-template <int R>
+template <int R, typename Index>
 __device__ inline int wave_frontier(const double (&vT)[R], const double (&vE)[R], double tl,
-                                    double el, int ibase, int S, const Scratch &sc, double *oT,
+                                    double el, const Index &index, const Scratch &sc, double *oT,
                                     double *oE, int32_t *oI)
 {
     const int lane = threadIdx.x & 63;
     wave_min2_f64(tl, el);
     const uint64_t tab = dbits(tl), ezb = dbits(el);
     if (tab >= KR_INF_BITS) return 0;  // no valid candidate
-    const Key A = chunk_pick<R>(vT, vE, ibase, S, [&](int r) { return dbits(vT[r]) == tab; });
+    const Key A = chunk_pick<R>(vT, vE, index, [&](int r) { return dbits(vT[r]) == tab; });
     const double TA = bitsd(A.t), EA = bitsd(A.e), EZ = el;
     const int32_t iA = A.i;
     const bool single = A.e == ezb;  // A has the least energy too: A is Z, nothing beats it
     int nkeep = 0;                   // kept points strictly inside the box
     if (!single) {
-        const Key Z = chunk_pick<R>(vT, vE, ibase, S, [&](int r) { return dbits(vE[r]) == ezb; });
+        const Key Z = chunk_pick<R>(vT, vE, index, [&](int r) { return dbits(vE[r]) == ezb; });
         const double TZ = bitsd(Z.t);
         const int32_t iZ = Z.i;
         uint32_t rows = 0;
@@ -192,7 +192,7 @@ __device__ inline int wave_frontier(const double (&vT)[R], const double (&vE)[R]
                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
                         sc.T[q] = vT[r];
                         sc.E[q] = vE[r];
-                        sc.I[q] = ibase + r * S;
+                        sc.I[q] = index(r);
                     }
                     base += __popcll(m);
                 }
@@ -237,7 +237,7 @@ __device__ inline int wave_frontier(const double (&vT)[R], const double (&vE)[R]
 #pragma unroll
                 for (int r = 0; r < R; ++r)
                     if (rows >> r & 1u) {
-                        const Key c{dbits(vT[r]), dbits(vE[r]), ibase + r * S};
+                        const Key c{dbits(vT[r]), dbits(vE[r]), index(r)};
                         if (c.t < zt && c.e < bound && kless(c, loc)) loc = c;
                     }
                 const Key w = wave_min_key(loc);
