@@ -124,15 +124,13 @@ bool pair_plan(EvalArgs *a)
     a->q_c = (int)(a->q_f + 6 * (int64_t)a->n_pos * a->S);  // 6-double records
     constexpr int NW = KR_PAIR_WAVES;
     const int64_t pairs = (int64_t)a->n_pos * a->S;
-    // one set per wave, and room for the pairs' own parts before that
-    a->q_sc = a->q_c + (int)std::max<int64_t>(NW * 6 * 64, 2 * pairs);
+    a->q_sc = a->q_c + (int)(2 * pairs);  // the pairs' own parts
     // scratch T, E, indices per wave; room for two 16-bit champions per position before that
     a->q_l = a->q_sc + (int)std::max<int64_t>(NW * (64 + 64 + 32), (a->n_pos + 1) / 2);
     const int64_t lds = a->q_l + 2 * a->S + (pairs + 3) / 4;
-    // taken where everything but the list and the parts' overhang fits the budget (those are
-    // a few KB, so that up to 70 KB are asked for)
-    const int64_t base = a->q_c + NW * 6 * 64 + NW * (64 + 64 + 32);
-    if ((size_t)base * 8 > kLdsBudget) return false;
+    // slabs of the sums and the fresh table that leave 17 KB of the budget; the largest of
+    // them ask for up to 70 KB in all
+    if ((size_t)(a->q_c + NW * (6 * 64 + 160)) * 8 > kLdsBudget) return false;
     a->pair = 1;
     a->lds_doubles = (int)lds;
     // each wave's slab-end reduction sorts in its share of the second-phase tables (20

@@ -31,7 +31,7 @@
 //    in the rounded results as well, and the frontier is the same, point for point.
 // Of the two-comm workload's 264 pairs per slab 9 are left on average, and a launch position
 // and SM choice take 8 + 9 evaluations instead of 264 to 8 (kernel 931 us with all of them,
-// 492 us without).
+// 370 us without).
 // A phase is kept as the values it adds to the energy sum and to the time, in the
 // order the walk adds them.  A candidate applies them to its own sums in that order,
 // so every candidate gets the roundings of the plain walk, operation for operation.
@@ -57,10 +57,13 @@ struct alignas(16) PairRec {
 // galloping, then bisection.  The predicate is monotone in j (the running sums never
 // decrease and rounding is monotone), so this is the j at which a left-to-right scan
 // of whole kernels stops.
+// hint: a guess at j, the search starts there if it is no overshoot (launch positions come
+// in ascending order, so a phase ends at or after the kernel where the one before did).
 __device__ __forceinline__ int pair_scan(const ColRec *AB, int S1, int s, int i0, int N,
-                                         double base, double rb)
+                                         double base, double rb, int hint = 0)
 {
     int lo = i0, step = 1;
+    if (hint > i0 && AB[hint * S1 + s].a - base <= rb) lo = hint;
     while (lo + step <= N && AB[(lo + step) * S1 + s].a - base <= rb) {
         lo += step;
         step <<= 1;
@@ -81,7 +84,7 @@ __device__ __forceinline__ int pair_scan(const ColRec *AB, int S1, int s, int i0
 // the budget leaves; then the rest of the interrupted kernel and the remaining kernels.
 __device__ __forceinline__ PairRec pair_phase(const double *Lt, const double *Lp,
                                               const ColRec *AB, int S1, int N, int s, int i,
-                                              double w, double tc)
+                                              double w, double tc, int &hint)
 {
     PairRec o{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     double used = 0.0;
@@ -104,7 +107,8 @@ __device__ __forceinline__ PairRec pair_phase(const double *Lt, const double *Lp
     if (!spent) {
         const double rb = tc - used;
         const ColRec zi = AB[i * S1 + s];
-        const int j = pair_scan(AB, S1, s, i, N, zi.a, rb);
+        const int j = pair_scan(AB, S1, s, i, N, zi.a, rb, hint);
+        hint = j;
         const ColRec zj = AB[j * S1 + s];
         o.eb = zj.b - zi.b;
         if (j == N) {
@@ -274,21 +278,22 @@ __device__ __forceinline__ void wave_max2_f64(double &x, double &y)
 // Block (p, b): NW waves sharing the slabs of partition p, frequencies [b*fb,
 // min(F, (b+1)*fb)), one slab at a time.  LDS (in doubles): t slab [N][S1] at 0, pw slab
 // at q_pw, running sums {A, B} [N + 1][S1] at q_ab (column 0 the all-SM state), the
-// fresh second-phase table [n_pos][S] at q_f, each wave's continuing second phases [64]
-// at q_c (the pairs' own parts before those), each wave's filter scratch at q_sc (the
+// fresh second-phase table [n_pos][S] at q_f, the pairs' own parts [n_pos][S] at q_c, each
+// wave's filter scratch at q_sc (the
 // positions' champions before that), the list of the pairs kept at q_l, after the second
 // comm kernel's times and energies [2][S].  Launch positions p1 go to the waves in
-// snake order (0, 1, .., NW - 1, NW - 1, .., 0, 0, 1, ..); a wave is a unit of its own (slot
+// snake order (0, 1, .., NW - 1, NW - 1, .., 0, 0, 1, .., see pair_owner); a wave is a unit of its own (slot
 // and count), so waves never share output.
 // Lane (s1, s2) evaluates, for each p1, the candidate that continues with s2, then every
 // S-th of the kept pairs from the s2-th on.  Each chunk's frontier goes to the
 // wave's slot; at the end of a slab those points (usually many times the slab's own
 // frontier) are read back into the second-phase tables, idle by then, sorted, and
 // replaced in place by their frontier, when they fit there.  SC > 0 fixes the number of
-// SM choices at compile time; FN also fixes the two-comm workload's 48 kernels and 33
+// SM choices at compile time (four blocks share a compute unit then, by registers and LDS:
+// 370 us against 444 us with three); FN also fixes the two-comm workload's 48 kernels and 33
 // launch positions.
 template <int R, int W, int NW, int SC, bool FN>
-__global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, UnitOut o)
+__global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kernel(EvalArgs a, UnitOut o)
 {
     extern __shared__ __attribute__((aligned(16))) double lds[];
     static_assert(!FN || SC > 0, "the fixed shape fixes the SM choices too");
@@ -298,7 +303,6 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
     double *const Lt = lds, *const Lp = lds + a.q_pw;
     ColRec *const AB = (ColRec *)(lds + a.q_ab);
     PairRec *const Fr = (PairRec *)(lds + a.q_f);
-    PairRec *const Cw = (PairRec *)(lds + a.q_c) + 64 * wave;
     double *const scw = lds + a.q_sc + 160 * wave;
     const Scratch sc{scw, scw + 64, (int32_t *)(scw + 128), 64};
     const int p = blockIdx.x / a.nfb, fbk = blockIdx.x - p * a.nfb;
@@ -381,8 +385,9 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
                 ltc[sF] = tcF;
                 lct[sF] = ctF;
             }
+            int hint = 0;
             for (int q = g; q < np; q += G) {
-                const PairRec o = q < N ? pair_phase(Lt, Lp, AB, S1, N, sF + 1, q, 1.0, tcF)
+                const PairRec o = q < N ? pair_phase(Lt, Lp, AB, S1, N, sF + 1, q, 1.0, tcF, hint)
                                         : PairRec{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
                 const ColRec z = AB[q * S1];
                 const double x = (z.a + tcF) + o.el4;
@@ -476,67 +481,83 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
         __syncthreads();
         const int nk = s_kept;
 
-        for (int p1 = 0; p1 < np; ++p1) {
-            if (pair_owner(p1, NW) != wave) continue;
-            // compute up to p1 in the all-SM state, then the first comm phase
+        // What the candidates of launch position p1 and this lane's SM choices share.
+        struct First {
+            int j1;             // the first comm phase ends in kernel j1
+            double Ec1, tau1;   // energy and time at its end
+            double Eca, used2;  // and with the interrupted kernel finished, and its time
+            ColRec zi2;         // running sums from there on, in the all-SM state
+            PairRec rec;        // the second phase that continues at once
+        };
+        int hint1 = 0, hint2 = 0;
+        auto first_phase = [&](int p1) {
+            First o;
             const int sa1 = s1 + 1;
             const ColRec z0 = AB[p1 * S1], zp = AB[p1 * S1 + sa1];
-            const int j1 = p1 < N ? pair_scan(AB, S1, sa1, p1, N, zp.a, tc1) : N;
+            const int j1 = p1 < N ? pair_scan(AB, S1, sa1, p1, N, zp.a, tc1, hint1) : N;
+            hint1 = j1;
             const ColRec zj = AB[j1 * S1 + sa1];
-            double Ec1 = z0.b + (zj.b - zp.b);
-            const double tau1 = z0.a + tc1;
+            o.j1 = j1;
+            o.Ec1 = z0.b + (zj.b - zp.b);
+            o.tau1 = z0.a + tc1;
             double w1 = 1.0;
             if (j1 < N) {
                 const double r1 = tc1 - (zj.a - zp.a);
-                Ec1 = Ec1 + Lp[j1 * S1 + sa1] * r1;
+                o.Ec1 = o.Ec1 + Lp[j1 * S1 + sa1] * r1;
                 w1 = 1.0 - r1 / Lt[j1 * S1 + sa1];
                 if (w1 < 0.0) w1 = 0.0;
             }
             // compute on to p2 in the all-SM state (candidates with j1 < p2)
-            double Eca = Ec1, used2 = 0.0;
+            o.Eca = o.Ec1;
+            o.used2 = 0.0;
             int i2 = j1;
             if (j1 < N && w1 < 1.0) {
                 const double need = w1 * Lt[j1 * S1];
-                Eca = Ec1 + Lp[j1 * S1] * need;
-                used2 = need;
+                o.Eca = o.Ec1 + Lp[j1 * S1] * need;
+                o.used2 = need;
                 i2 = j1 + 1;
             }
-            const ColRec zi2 = AB[i2 * S1];
+            o.zi2 = AB[i2 * S1];
             // the second comm phase continuing the first one's progress (p2 <= j1)
-            Cw[lane] = j1 < N ? pair_phase(Lt, Lp, AB, S1, N, s2 + 1, j1, w1, tc2)
-                              : PairRec{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-            wave_lds_fence();
+            o.rec = j1 < N ? pair_phase(Lt, Lp, AB, S1, N, s2 + 1, j1, w1, tc2, hint2)
+                           : PairRec{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            return o;
+        };
+        // time and energy from a second phase: st2 its start, Ec the energy before it
+        auto finish = [&](const PairRec &q, double st2, double Ec, double tcs, double cts,
+                          double &T, double &E) {
+            Ec = Ec + q.ea;
+            Ec = Ec + q.eb;
+            Ec = Ec + q.ec;
+            Ec = Ec + q.a4;
+            Ec = Ec + q.b4;
+            T = (st2 + tcs) + q.el4;
+            E = p_static * T;
+            E = E + Ec;
+            E = E + ct1;
+            E = E + cts;
+        };
+        // A chunk of R slots per position: the continuing candidate first, then rounds of kept
+        // pairs.  (Two positions sharing eight slots: 399 us, for the registers they take.)
+        for (int p1 = 0; p1 < np; ++p1) {
+            if (pair_owner(p1, NW) != wave) continue;
+            const First o = first_phase(p1);
             // pair rank of (p1, p2): ppb + p2
             const int ppb = p1 * np - p1 * (p1 - 1) / 2 - p1;
             const int i1 = f * a.Cf + s1 * S;
-            // time and energy from a second phase: st2 its start, Ec the energy before it
-            auto finish = [&](const PairRec &q, double st2, double Ec, double tcs, double cts,
-                              double &T, double &E) {
-                Ec = Ec + q.ea;
-                Ec = Ec + q.eb;
-                Ec = Ec + q.ec;
-                Ec = Ec + q.a4;
-                Ec = Ec + q.b4;
-                T = (st2 + tcs) + q.el4;
-                E = p_static * T;
-                E = E + Ec;
-                E = E + ct1;
-                E = E + cts;
-            };
-            // chunks of R slots: the continuing candidate first, then rounds of kept pairs
             for (int e0 = -S; e0 < nk; e0 += R * S) {
                 double vT[R], vE[R];
                 int32_t vI[R];
                 double tl = INFINITY, el = INFINITY;
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const int e = e0 + r * S;  // this round's first entry of the list
+                    const int e = e0 + r * S;  // this round's first list entry
                     vT[r] = INFINITY;
                     vE[r] = INFINITY;
                     vI[r] = 0;
                     if (e >= nk) continue;  // uniform
                     if (r == 0 && e < 0) {
-                        finish(Cw[lane], tau1, Ec1, tc2, ct2, vT[r], vE[r]);
+                        finish(o.rec, o.tau1, o.Ec1, tc2, ct2, vT[r], vE[r]);
                         vI[r] = i1 + (ppb + p1) * SS + s2;
                         vT[r] = live ? vT[r] : INFINITY;
                         vE[r] = live ? vE[r] : INFINITY;
@@ -545,10 +566,10 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
                         const int q = in ? list[e + s2] : 0;
                         const int p2 = q / S, c = q - p2 * S;
                         const ColRec z2 = AB[p2 * S1];
-                        const bool valid = in && j1 < p2;  // fresh: compute has not reached p2
+                        const bool valid = in && o.j1 < p2;  // compute has not reached p2
                         double T, E;
-                        finish(Fr[q], tau1 + (used2 + (z2.a - zi2.a)), Eca + (z2.b - zi2.b), ltc[c],
-                               lct[c], T, E);
+                        finish(Fr[q], o.tau1 + (o.used2 + (z2.a - o.zi2.a)),
+                               o.Eca + (z2.b - o.zi2.b), ltc[c], lct[c], T, E);
                         vI[r] = i1 + (ppb + p2) * SS + c;
                         vT[r] = valid ? T : INFINITY;
                         vE[r] = valid ? E : INFINITY;
@@ -559,7 +580,6 @@ __global__ void __launch_bounds__(64 * NW) eval_filter_pair_kernel(EvalArgs a, U
                 count += wave_frontier<R>(vT, vE, tl, el, [&](int r) { return vI[r]; }, sc,
                                           oT + count, oE + count, oI + count);
             }
-            wave_lds_fence();  // the continuing phase of this p1 is read
         }
         __syncthreads();  // every wave is done with the slab's tables
         const int ns = count - cs;
