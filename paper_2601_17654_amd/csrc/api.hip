@@ -410,7 +410,7 @@ size_t kr_compose_frontiers_workspace(int32_t n_parts, int32_t n_bins)
     c.take<double>(B + 8 * P);
     c.take<int32_t>(P);
     c.take<double>(P * B);
-    c.take<int32_t>(1);
+    c.take<int32_t>(2);
     c.take<double>((B + KR_ST_CHUNK - 1) / KR_ST_CHUNK);
     c.take<int32_t>((B + KR_ST_CHUNK - 1) / KR_ST_CHUNK);
     return c.used;
@@ -445,7 +445,7 @@ kr_status kr_compose_frontiers(int32_t n_parts, const int64_t *off, const double
     w.oe = c.take<double>(B + 8 * P);
     w.occ = c.take<int32_t>(P);
     w.Fh = c.take<double>(P * B);
-    w.ticket = c.take<int32_t>(1);
+    w.ticket = c.take<int32_t>(2);
     w.chmin = c.take<double>((B + KR_ST_CHUNK - 1) / KR_ST_CHUNK);
     w.chcnt = c.take<int32_t>((B + KR_ST_CHUNK - 1) / KR_ST_CHUNK);
     ComposeArgs a;

@@ -37,6 +37,8 @@ __device__ __forceinline__ int32_t load_l2(const int32_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A NaN pattern no step writes: an entry that has not been published yet
+#define KR_UNSET 0x7FF4B1A5C0DE0000ull
 #define KR_MP_W 256     // output bins per tile
 #define KR_MP_Q 4       // quarters of a partition's records per tile (block = W * Q threads)
 #define KR_MP_HCAP 1024 // largest partition offset range staged in LDS
@@ -56,24 +58,12 @@ __device__ __forceinline__ void store_dev(int32_t *p, int32_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__global__ void compose_init_kernel(ComposeArgs a, ComposeWs w)
-{
-    if (threadIdx.x == 0) {
-        *a.status = KR_OK;
-        *w.ticket = 0;
-    }
-}
-
-// Per-partition time range.
+// Per-partition time range, and the partition's verdict (in occ, until it is binned).
 __global__ void __launch_bounds__(KR_BLOCK) compose_range_kernel(ComposeArgs a, ComposeWs w)
 {
     __shared__ double sc[KR_WAVES];
     const int k = blockIdx.x;
     const int64_t lo = a.off[k], hi = a.off[k + 1];
-    if (hi <= lo) {
-        if (threadIdx.x == 0) *a.status = KR_EINVAL;
-        return;
-    }
     double mn = INFINITY, mx = -INFINITY;
     bool bad = false;  // a non-finite time, or an energy that is not a finite value >= 0
     for (int64_t j = lo + threadIdx.x; j < hi; j += KR_BLOCK) {
@@ -82,12 +72,13 @@ __global__ void __launch_bounds__(KR_BLOCK) compose_range_kernel(ComposeArgs a, 
         mx = t > mx ? t : mx;
         bad = bad || !(dbits(fabs(t)) < KR_INF_BITS) || !(dbits(a.E[j] + 0.0) < KR_INF_BITS);
     }
-    if (__ballot(bad) && (threadIdx.x & 63) == 0) store_dev(a.status, (int32_t)KR_ENONFINITE);
+    bad = __syncthreads_or(bad);
     mn = block_reduce(mn, (double)INFINITY, MinF64(), sc);
     mx = block_reduce(mx, -(double)INFINITY, MaxF64(), sc);
     if (threadIdx.x == 0) {
         w.tmin[k] = mn;
         w.range[k] = mx - mn;
+        w.occ[k] = hi <= lo ? KR_EINVAL : bad ? KR_ENONFINITE : KR_OK;
     }
 }
 
@@ -101,8 +92,28 @@ __global__ void __launch_bounds__(KR_BLOCK) compose_setup_kernel(ComposeArgs a, 
     __shared__ double s_delta, s_tsum;
     __shared__ double s_range[kChunk], s_tmin[kChunk];
     __shared__ int64_t sc[KR_WAVES];
-    if (*a.status != KR_OK) return;
     const int P = a.P, B = a.B;
+    {
+        // the verdict, and what the later launches count in (cleared here, so that neither
+        // takes a launch of its own)
+        bool empty = false, bad = false;
+        for (int k = threadIdx.x; k < P; k += KR_BLOCK) {
+            empty = empty || w.occ[k] == KR_EINVAL;
+            bad = bad || w.occ[k] == KR_ENONFINITE;
+        }
+        for (int c = threadIdx.x; c < (B + KR_ST_CHUNK - 1) / KR_ST_CHUNK; c += KR_BLOCK) {
+            ((uint64_t *)w.chmin)[c] = KR_UNSET;
+            w.chcnt[c] = -1;
+        }
+        empty = __syncthreads_or(empty);
+        bad = __syncthreads_or(bad);
+        if (threadIdx.x == 0) {
+            *a.status = empty ? KR_EINVAL : bad ? KR_ENONFINITE : KR_OK;
+            w.ticket[0] = 0;
+            w.ticket[1] = 0;
+        }
+        if (empty || bad) return;
+    }
     // the sums in partition order, by thread 0 from LDS copies the block loads together
     double R = 0.0, tmin_sum = 0.0;
     for (int k0 = 0; k0 < P; k0 += kChunk) {
@@ -258,7 +269,6 @@ __device__ __forceinline__ void bin_partition(const ComposeArgs &a, const Compos
 // device-scope relaxed atomic accesses, which are coherent across the chip without
 // cache maintenance; each is written at most once per launch, after the fill kernel.
 #define KR_WF_POLLS (1 << 22)
-#define KR_UNSET 0x7FF4B1A5C0DE0000ull
 
 
 // Whether bin x of row k is read by another tile: within M_{k+1} of its tile's right
@@ -772,48 +782,46 @@ __device__ __forceinline__ T block_scan_excl(T v, T identity, Op op, T *lds, T *
     return op(before, ex);
 }
 
-// Bins whose value is strictly below every earlier bin, in three passes over chunks of
-// KR_ST_CHUNK bins, one block each: the least value of every chunk; then per chunk the
-// least value before it (from the chunk minima), a prefix-minimum scan inside it and
-// its count of kept bins; then the output position from the counts before it, and the
-// writes.  Thread t holds bins 4t .. 4t + 3 of its chunk.
+// Bins whose value is strictly below every earlier bin: a block per chunk of KR_ST_CHUNK
+// bins.  It publishes its chunk's least value, takes the least of the chunks before it from
+// theirs, scans its bins, publishes its count of kept bins, and places them behind those of
+// the chunks before.  Chunks are handed out by ticket, so a block waits only for blocks that
+// started before it.  (Three launches, one per pass, cost 10 us and their gaps; the call on
+// 4 partitions and 1,024 bins is launches and nothing else.)  Thread t holds bins
+// 4t .. 4t + 3 of its chunk.
 #define KR_ST_NT 256
 
-__device__ __forceinline__ double st_bin(const ComposeArgs &a, int b)
-{
-    return b < a.B ? a.F_out[b] : INFINITY;
-}
-
-__global__ void __launch_bounds__(KR_ST_NT) staircase_min_kernel(ComposeArgs a, ComposeWs w)
+__global__ void __launch_bounds__(KR_ST_NT) staircase_kernel(ComposeArgs a, ComposeWs w)
 {
     __shared__ double sm[KR_ST_NT / 64];
-    const int base = blockIdx.x * KR_ST_CHUNK;
-    double m = INFINITY;
-#pragma unroll
-    for (int q = 0; q < KR_ST_CHUNK / KR_ST_NT; ++q)
-        m = MinF64()(m, st_bin(a, base + q * KR_ST_NT + threadIdx.x));
-    double tot;
-    block_scan_excl<KR_ST_NT>(m, (double)INFINITY, MinF64(), sm, &tot);
-    if (threadIdx.x == 0) w.chmin[blockIdx.x] = tot;
-}
-
-// Least value before this chunk, and this thread's kept bins (bit q: bin 4t + q).
-__device__ __forceinline__ uint32_t st_keep(const ComposeArgs &a, const ComposeWs &w,
-                                            double *sm, double (&v)[4])
-{
-    double before = INFINITY;
-    for (int c = threadIdx.x; c < (int)blockIdx.x; c += KR_ST_NT)
-        before = MinF64()(before, w.chmin[c]);
-    double tot;
-    block_scan_excl<KR_ST_NT>(before, (double)INFINITY, MinF64(), sm, &tot);
-    const int b0 = blockIdx.x * KR_ST_CHUNK + 4 * threadIdx.x;
-    double tm = INFINITY;
+    __shared__ int32_t si[KR_ST_NT / 64];
+    __shared__ int32_t s_chunk;
+    // a composition that failed (status set by an earlier kernel) has no staircase
+    if (*a.status != KR_OK) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *a.n_stair = 0;
+        return;
+    }
+    if (threadIdx.x == 0) s_chunk = atomicAdd(w.ticket + 1, 1);
+    __syncthreads();
+    const int chunk = s_chunk;
+    const int b0 = chunk * KR_ST_CHUNK + 4 * threadIdx.x;
+    double v[4], tm = INFINITY;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        v[q] = st_bin(a, b0 + q);
+        v[q] = b0 + q < a.B ? a.F_out[b0 + q] : INFINITY;
         tm = MinF64()(tm, v[q]);
     }
-    double run = block_scan_excl<KR_ST_NT>(tm, (double)INFINITY, MinF64(), sm, &before);
+    double least;
+    double run = block_scan_excl<KR_ST_NT>(tm, (double)INFINITY, MinF64(), sm, &least);
+    if (threadIdx.x == 0) store_dev((uint64_t *)w.chmin + chunk, dbits(least));
+    double before = INFINITY;
+    for (int c = threadIdx.x; c < chunk; c += KR_ST_NT) {
+        uint64_t x;
+        while ((x = load_l2((const uint64_t *)w.chmin + c)) == KR_UNSET) __builtin_amdgcn_s_sleep(1);
+        before = MinF64()(before, bitsd(x));
+    }
+    double tot;
+    block_scan_excl<KR_ST_NT>(before, (double)INFINITY, MinF64(), sm, &tot);
     run = MinF64()(run, tot);
     uint32_t k = 0;
 #pragma unroll
@@ -822,40 +830,19 @@ __device__ __forceinline__ uint32_t st_keep(const ComposeArgs &a, const ComposeW
             k |= 1u << q;
             run = v[q];
         }
-    return k;
-}
-
-__global__ void __launch_bounds__(KR_ST_NT) staircase_count_kernel(ComposeArgs a, ComposeWs w)
-{
-    __shared__ double sm[KR_ST_NT / 64];
-    __shared__ int32_t si[KR_ST_NT / 64];
-    double v[4];
-    const uint32_t k = st_keep(a, w, sm, v);
     int32_t n;
-    block_scan_excl<KR_ST_NT>((int32_t)__popc(k), 0, SumI32(), si, &n);
-    if (threadIdx.x == 0) w.chcnt[blockIdx.x] = n;
-}
-
-__global__ void __launch_bounds__(KR_ST_NT) staircase_write_kernel(ComposeArgs a, ComposeWs w)
-{
-    __shared__ double sm[KR_ST_NT / 64];
-    __shared__ int32_t si[KR_ST_NT / 64];
-    const int nb = gridDim.x;
-    int32_t before = 0, all = 0;
-    for (int c = threadIdx.x; c < nb; c += KR_ST_NT) {
-        const int32_t x = w.chcnt[c];
-        if (c < (int)blockIdx.x) before += x;
-        all += x;
+    int32_t pos = block_scan_excl<KR_ST_NT>((int32_t)__popc(k), 0, SumI32(), si, &n);
+    if (threadIdx.x == 0) store_dev(w.chcnt + chunk, n);
+    int32_t earlier = 0;
+    for (int c = threadIdx.x; c < chunk; c += KR_ST_NT) {
+        int32_t x;
+        while ((x = load_l2(w.chcnt + c)) < 0) __builtin_amdgcn_s_sleep(1);
+        earlier += x;
     }
-    int32_t tb, ta;
-    block_scan_excl<KR_ST_NT>(before, 0, SumI32(), si, &tb);
-    block_scan_excl<KR_ST_NT>(all, 0, SumI32(), si, &ta);
-    double v[4];
-    const uint32_t k = st_keep(a, w, sm, v);
-    int32_t n;
-    int32_t pos = tb + block_scan_excl<KR_ST_NT>((int32_t)__popc(k), 0, SumI32(), si, &n);
+    int32_t first;
+    block_scan_excl<KR_ST_NT>(earlier, 0, SumI32(), si, &first);
+    pos += first;
     const double delta = a.info[0], tmin_sum = a.info[1];
-    const int b0 = blockIdx.x * KR_ST_CHUNK + 4 * threadIdx.x;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         if (k >> q & 1u) {
@@ -864,14 +851,12 @@ __global__ void __launch_bounds__(KR_ST_NT) staircase_write_kernel(ComposeArgs a
             a.stair_E[pos] = v[q];
             ++pos;
         }
-    // a composition that failed (status set by an earlier kernel) has no staircase
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.n_stair = *a.status == KR_OK ? ta : 0;
+    if (chunk == (int)gridDim.x - 1 && threadIdx.x == 0) *a.n_stair = first + n;
 }
 
 hipError_t launch_compose(const ComposeArgs &a, const ComposeWs &w, hipEvent_t *minplus_ev,
                           hipStream_t st)
 {
-    hipLaunchKernelGGL(compose_init_kernel, dim3(1), dim3(64), 0, st, a, w);
     hipLaunchKernelGGL(compose_range_kernel, dim3(a.P), dim3(KR_BLOCK), 0, st, a, w);
     hipLaunchKernelGGL(compose_setup_kernel, dim3(1), dim3(KR_BLOCK), 0, st, a, w);
     hipLaunchKernelGGL(compose_bin_fill_kernel, dim3(2 * a.P - 1), dim3(KR_BLOCK), 0, st, a, w);
@@ -879,12 +864,8 @@ hipError_t launch_compose(const ComposeArgs &a, const ComposeWs &w, hipEvent_t *
     if (minplus_ev) (void)hipEventRecord(minplus_ev[0], st);
     hipLaunchKernelGGL(minplus_wavefront_kernel, dim3(G), dim3(KR_MP_W * KR_MP_Q), 0, st, a, w);
     if (minplus_ev) (void)hipEventRecord(minplus_ev[1], st);
-    {
-        const int nb = (a.B + KR_ST_CHUNK - 1) / KR_ST_CHUNK;
-        hipLaunchKernelGGL(staircase_min_kernel, dim3(nb), dim3(KR_ST_NT), 0, st, a, w);
-        hipLaunchKernelGGL(staircase_count_kernel, dim3(nb), dim3(KR_ST_NT), 0, st, a, w);
-        hipLaunchKernelGGL(staircase_write_kernel, dim3(nb), dim3(KR_ST_NT), 0, st, a, w);
-    }
+    hipLaunchKernelGGL(staircase_kernel, dim3((a.B + KR_ST_CHUNK - 1) / KR_ST_CHUNK), dim3(KR_ST_NT),
+                       0, st, a, w);
     return hipGetLastError();
 }
 

@@ -142,7 +142,7 @@ struct ComposeWs {
     double *oe;            // [B + 8P]
     int32_t *occ;          // [P]
     double *Fh;            // [P][B] step history of the wavefront min-plus
-    int32_t *ticket;       // [1] tile tickets of the wavefront min-plus (reset per call)
+    int32_t *ticket;       // [2] tickets: min-plus tiles, staircase chunks (reset per call)
     double *chmin;         // [ceil(B / KR_ST_CHUNK)] least value of each staircase chunk
     int32_t *chcnt;        // [ceil(B / KR_ST_CHUNK)] staircase bins of each chunk
 };
