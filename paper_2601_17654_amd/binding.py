@@ -107,6 +107,25 @@ def _check_status(fn: str, status: Optional[torch.Tensor]) -> None:
         _check(fn, int(status.item()))
 
 
+class _Offsets:
+    """Output offsets of a filter, int64 [n_seg + 1], and behind them the status word of its
+    input check, so that the count of points and the verdict come back in one copy."""
+
+    def __init__(self, n_seg: int):
+        self.words = torch.empty(n_seg + 2, dtype=torch.int64, device="cuda")
+        self.off = self.words[:n_seg + 1]
+
+    def status_ptr(self):
+        return ctypes.c_void_p(self.words.data_ptr() + 8 * (self.words.numel() - 1))
+
+    def read(self, fn: str, validate: bool) -> int:
+        """Waits for the stream: the count, after the verdict if there is one."""
+        total, status = self.words[-2:].tolist()
+        if validate:
+            _check(fn, ctypes.c_int32(status & 0xFFFFFFFF).value)
+        return total
+
+
 def _space(space) -> KrSpace:
     return KrSpace(space.n_parts, space.n_kernels, space.n_comm, space.n_freq, space.n_sm,
                    space.n_pos, float(space.p_static))
@@ -194,14 +213,15 @@ class Frontier:
     E: torch.Tensor     # float64 [total]
 
 
-def _finish_frontier(off, idx, T, E, cap, sync):
+def _finish_frontier(out: _Offsets, idx, T, E, cap, sync, validate, fn):
+    if not sync and not validate:
+        return Frontier(out.off, idx, T, E), True
+    total = out.read(fn, validate)
     if not sync:
-        return Frontier(off, idx, T, E), True
-    torch.cuda.current_stream().synchronize()
-    total = int(off[-1].item())
+        return Frontier(out.off, idx, T, E), True
     if total > cap:
         return None, total
-    return Frontier(off, idx[:total], T[:total], E[:total]), True
+    return Frontier(out.off, idx[:total], T[:total], E[:total]), True
 
 
 NOALLOC_MAX_POINTS, NOALLOC_MAX_SEGS = 1 << 20, 1 << 16
@@ -223,28 +243,28 @@ def pareto_filter(T, E, seg_off, cap: Optional[int] = None, sync: bool = True,
     if T.numel() != n_total or E.numel() != n_total:
         raise ValueError("T/E must hold seg_off[-1] points")
     seg_dev = torch.from_numpy(seg_host).cuda()
+    check = sync if validate is None else bool(validate)
     while True:
         c = int(cap) if cap is not None else min(n_total, max(4096 * max(n_seg, 1), 1))
-        off = torch.empty(n_seg + 1, dtype=torch.int64, device="cuda")
+        out = _Offsets(n_seg)
         idx = torch.empty(max(c, 1), dtype=torch.int32, device="cuda")
         oT = torch.empty(max(c, 1), dtype=torch.float64, device="cuda")
         oE = torch.empty(max(c, 1), dtype=torch.float64, device="cuda")
-        status = _status_word(sync if validate is None else validate)
+        status = out.status_ptr() if check else None
         if noalloc:
             fn = "kr_pareto_filter_noalloc"
             rc = _lib.kr_pareto_filter_noalloc(n_total, _ptr(T), _ptr(E), _ptr(seg_dev), n_seg, c,
-                                               _ptr(off), _ptr(idx), _ptr(oT), _ptr(oE),
-                                               _ptr(status), _stream())
+                                               _ptr(out.off), _ptr(idx), _ptr(oT), _ptr(oE),
+                                               status, _stream())
         else:
             fn = "kr_pareto_filter"
             wsb = _lib.kr_pareto_filter_workspace(n_total, n_seg)
             ws = _workspace(wsb)
             rc = _lib.kr_pareto_filter(n_total, _ptr(T), _ptr(E), _ptr(seg_dev), n_seg, c,
-                                       _ptr(off), _ptr(idx), _ptr(oT), _ptr(oE), _ptr(status),
+                                       _ptr(out.off), _ptr(idx), _ptr(oT), _ptr(oE), status,
                                        _ptr(ws), wsb, _stream())
         _check(fn, rc)
-        _check_status(fn, status)
-        fr, ok = _finish_frontier(off, idx, oT, oE, c, sync)
+        fr, ok = _finish_frontier(out, idx, oT, oE, c, sync, check, fn)
         if fr is not None:
             return fr
         cap = ok  # the exact size
@@ -263,20 +283,20 @@ def evaluate_and_filter(space, t, pw, tc, pc, cap: Optional[int] = None,
     wsb = _lib.kr_evaluate_and_filter_workspace(ctypes.byref(sp))
     if wsb == 0:
         raise KrError("kr_evaluate_and_filter_workspace", KR_EUNSUPPORTED)
+    check = sync if validate is None else bool(validate)
     while True:
         c = int(cap) if cap is not None else min(space.n_parts * C, 4096 * space.n_parts)
-        off = torch.empty(space.n_parts + 1, dtype=torch.int64, device="cuda")
+        out = _Offsets(space.n_parts)
         idx = torch.empty(max(c, 1), dtype=torch.int32, device="cuda")
         oT = torch.empty(max(c, 1), dtype=torch.float64, device="cuda")
         oE = torch.empty(max(c, 1), dtype=torch.float64, device="cuda")
         ws = _workspace(wsb)
-        status = _status_word(sync if validate is None else validate)
         _check("kr_evaluate_and_filter",
                _lib.kr_evaluate_and_filter(ctypes.byref(sp), _ptr(t), _ptr(pw), _ptr(tc), _ptr(pc),
-                                           c, _ptr(off), _ptr(idx), _ptr(oT), _ptr(oE),
-                                           _ptr(status), _ptr(ws), wsb, _stream()))
-        _check_status("kr_evaluate_and_filter", status)
-        fr, ok = _finish_frontier(off, idx, oT, oE, c, sync)
+                                           c, _ptr(out.off), _ptr(idx), _ptr(oT), _ptr(oE),
+                                           out.status_ptr() if check else None, _ptr(ws), wsb,
+                                           _stream()))
+        fr, ok = _finish_frontier(out, idx, oT, oE, c, sync, check, "kr_evaluate_and_filter")
         if fr is not None:
             return fr
         cap = ok
