@@ -87,8 +87,18 @@ __device__ __forceinline__ void finish_tail(const Tail &q, double p_static, doub
 // are discarded); only their LDS addresses are clamped.  FX (32 kernels, 33 positions,
 // 32 SM choices: runs of 16 and 17 positions) makes the sizes and LDS offsets
 // immediates and lets every round but the last skip the validity selects.
+//
+// The registers decide how many waves share a SIMD, and a wave alone leaves it idle most of
+// the time.  Held to three waves, chunks of 10 to 14 took 214 us instead of 232 (14) and 120
+// instead of 135 (10); held to four, chunks of 4 to 8 took 99 instead of 106 (5) and 23.5
+// instead of 25.2 (7).  Chunks of 3 lost by four (143 against 135), and 17 are bound by LDS.
+constexpr int wave_occupancy(int R, int W)
+{
+    return R >= 4 && R <= 8 && W == 16 ? 4 : R >= 10 && R <= 14 ? 3 : 1;
+}
+
 template <int R, int W, int SC, bool FX>
-__global__ void __launch_bounds__(64) eval_filter_wave_kernel(EvalArgs a, UnitOut o)
+__global__ void __launch_bounds__(64, wave_occupancy(R, W)) eval_filter_wave_kernel(EvalArgs a, UnitOut o)
 {
     constexpr int K = KR_PAD;
     extern __shared__ double lds[];
