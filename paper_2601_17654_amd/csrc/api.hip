@@ -127,7 +127,7 @@ bool pair_plan(EvalArgs *a)
     a->q_sc = a->q_c + (int)(2 * pairs);  // the pairs' own parts
     // scratch T, E, indices per wave; room for two 16-bit champions per position before that
     a->q_l = a->q_sc + (int)std::max<int64_t>(NW * (64 + 64 + 32), (a->n_pos + 1) / 2);
-    const int64_t lds = a->q_l + 2 * a->S + (pairs + 3) / 4;
+    const int64_t lds = a->q_l + 2 * a->S + (2 * pairs + 3) / 4;
     // slabs of the sums and the fresh table that leave 17 KB of the budget; the largest of
     // them ask for up to 70 KB in all
     if ((size_t)(a->q_c + NW * (6 * 64 + 160)) * 8 > kLdsBudget) return false;

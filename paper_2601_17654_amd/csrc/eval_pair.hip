@@ -32,6 +32,12 @@
 // Of the two-comm workload's 264 pairs per slab 9 are left on average, and a launch position
 // and SM choice take 8 + 9 evaluations instead of 264 to 8 (kernel 931 us with all of them,
 // 370 us without).
+// Of what is evaluated, most is beaten in time and energy by the wave's best candidate of the
+// slab so far (least E + mean power T); the rest gathers in the wave's scratch, 64 candidates to
+// a frontier, instead of taking a frontier per launch position (with the end of the first comm
+// phase tabled and a slab's frontiers merged one point per lane: 373 -> 279 us).  What is left
+// is latency: of those 279 us the sums, the table and the pruning take about 65, the
+// positions' phases about 100.
 // A phase is kept as the values it adds to the energy sum and to the time, in the
 // order the walk adds them.  A candidate applies them to its own sums in that order,
 // so every candidate gets the roundings of the plain walk, operation for operation.
@@ -285,12 +291,12 @@ __device__ __forceinline__ void wave_max2_f64(double &x, double &y)
 // snake order (0, 1, .., NW - 1, NW - 1, .., 0, 0, 1, .., see pair_owner); a wave is a unit of its own (slot
 // and count), so waves never share output.
 // Lane (s1, s2) evaluates, for each p1, the candidate that continues with s2, then every
-// S-th of the kept pairs from the s2-th on.  Each chunk's frontier goes to the
-// wave's slot; at the end of a slab those points (usually many times the slab's own
-// frontier) are read back into the second-phase tables, idle by then, sorted, and
-// replaced in place by their frontier, when they fit there.  SC > 0 fixes the number of
+// S-th of the kept pairs from the s2-th on.  Frontiers of up to 64 gathered candidates go to
+// the wave's slot; if a slab wrote more than one, its points are read back at the end and
+// replaced in place by their frontier: up to 64 one per lane, more by a sort in the
+// second-phase tables, idle by then, when they fit there.  SC > 0 fixes the number of
 // SM choices at compile time (four blocks share a compute unit then, by registers and LDS:
-// 370 us against 444 us with three); FN also fixes the two-comm workload's 48 kernels and 33
+// 370 us against 444 us with three, before candidates were gathered); FN also fixes the two-comm workload's 48 kernels and 33
 // launch positions.
 template <int R, int W, int NW, int SC, bool FN>
 __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kernel(EvalArgs a, UnitOut o)
@@ -324,6 +330,7 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
     double *const ltc = lds + a.q_l, *const lct = ltc + S;   // [S] each
     int16_t *const list = (int16_t *)(lds + a.q_l + 2 * S);  // [np * S]
     const int npS = np * S;
+    int16_t *const first = list + npS;  // [np * S]: where the first comm phase ends
     // sort room of the slab-end reduction: this wave's share of the fresh and continuing
     // tables
     const int scap = a.pair_scap;
@@ -339,7 +346,7 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
         copy_to_lds_nw<W, NW>(a.t + pf * slab, Lt, slab);
         copy_to_lds_nw<W, NW>(a.pw + pf * slab, Lp, slab);
         const double *const cm = a.tc + pf * 2 * S, *const cpw = a.pc + pf * 2 * S;
-        const double tc1 = cm[s1], tc2 = cm[S + s2], tcF = cm[S + sF];
+        const double tc1 = cm[s1], tc2 = cm[S + s2], tcF = cm[S + sF], tcF1 = cm[sF];
         const double pc1 = cpw[s1], pc2 = cpw[S + s2];
         const double ct1 = pc1 * tc1, ct2 = pc2 * tc2;
         worst = max(worst, max(max(value_hi(tc1), value_hi(tc2)), max(value_hi(pc1), value_hi(pc2))));
@@ -385,10 +392,13 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
                 ltc[sF] = tcF;
                 lct[sF] = ctF;
             }
-            int hint = 0;
+            int hint = 0, hint1 = 0;
             for (int q = g; q < np; q += G) {
                 const PairRec o = q < N ? pair_phase(Lt, Lp, AB, S1, N, sF + 1, q, 1.0, tcF, hint)
                                         : PairRec{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+                if (q < N)
+                    hint1 = pair_scan(AB, S1, sF + 1, q, N, AB[q * S1 + sF + 1].a, tcF1, hint1);
+                first[q * S + sF] = (int16_t)(q < N ? hint1 : N);
                 const ColRec z = AB[q * S1];
                 const double x = (z.a + tcF) + o.el4;
                 Fr[q * S + sF] = o;
@@ -410,9 +420,9 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
         // Champions: per position the pair at it or later with the least Z + c X, for two
         // weights c around the slab's mean power (a time-leaning and an energy-leaning one).
         // Testing every pair against these two keeps 9 of 264, against all of them 7.
+        const double mean = zall.a > 0.0 ? p_static + zall.b / zall.a : p_static;
+        const double c0 = 0.25 * mean, c1 = 4.0 * mean;
         if (wave == 0) {
-            const double mean = zall.a > 0.0 ? p_static + zall.b / zall.a : p_static;
-            const double c0 = 0.25 * mean, c1 = 4.0 * mean;
             double l0 = INFINITY, l1 = INFINITY;  // least of the later positions (uniform)
             int a0 = 0, a1 = 0;
             for (int base = (np - 1) / 64 * 64; base >= 0; base -= 64) {
@@ -489,13 +499,12 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
             ColRec zi2;         // running sums from there on, in the all-SM state
             PairRec rec;        // the second phase that continues at once
         };
-        int hint1 = 0, hint2 = 0;
+        int hint2 = 0;
         auto first_phase = [&](int p1) {
             First o;
             const int sa1 = s1 + 1;
             const ColRec z0 = AB[p1 * S1], zp = AB[p1 * S1 + sa1];
-            const int j1 = p1 < N ? pair_scan(AB, S1, sa1, p1, N, zp.a, tc1, hint1) : N;
-            hint1 = j1;
+            const int j1 = first[p1 * S + s1];
             const ColRec zj = AB[j1 * S1 + sa1];
             o.j1 = j1;
             o.Ec1 = z0.b + (zj.b - zp.b);
@@ -537,6 +546,24 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
             E = E + ct1;
             E = E + cts;
         };
+        // The wave's best candidate of the slab so far, by E + mean T: what it beats in both
+        // time and energy is on no frontier.  (Two of them, with the weights above: 361 us
+        // against 333, for the registers and the second search.)
+        double best = INFINITY, bestT = INFINITY, bestE = INFINITY;
+        int nb = 0;     // candidates in the wave's scratch
+        int parts = 0;  // frontiers written
+        auto flush = [&]() {  // writes the scratch's frontier (nb > 0)
+            wave_lds_fence();
+            const int x = min(lane, nb - 1);
+            const double xT = sc.T[x], xE = sc.E[x];
+            const int32_t xI = sc.I[x];
+            const double fT[1] = {lane < nb ? xT : INFINITY}, fE[1] = {lane < nb ? xE : INFINITY};
+            wave_lds_fence();
+            count += wave_frontier<1>(fT, fE, fT[0], fE[0], [&](int) { return xI; }, sc, oT + count,
+                                      oE + count, oI + count);
+            nb = 0;
+            ++parts;
+        };
         // A chunk of R slots per position: the continuing candidate first, then rounds of kept
         // pairs.  (Two positions sharing eight slots: 399 us, for the registers they take.)
         for (int p1 = 0; p1 < np; ++p1) {
@@ -574,26 +601,91 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
                         vT[r] = valid ? T : INFINITY;
                         vE[r] = valid ? E : INFINITY;
                     }
+                    const bool beaten = bestT < vT[r] && bestE < vE[r];
+                    vT[r] = beaten ? INFINITY : vT[r];
+                    vE[r] = beaten ? INFINITY : vE[r];
                     tl = vmin(tl, vT[r]);
                     el = vmin(el, vE[r]);
                 }
-                count += wave_frontier<R>(vT, vE, tl, el, [&](int r) { return vI[r]; }, sc,
-                                          oT + count, oE + count, oI + count);
+                if (!__any(tl < INFINITY)) continue;
+                double g = INFINITY, hT = 0.0, hE = 0.0;  // this lane's least E + mean T
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const double v = vE[r] + mean * vT[r];
+                    hT = v < g ? vT[r] : hT;
+                    hE = v < g ? vE[r] : hE;
+                    g = v < g ? v : g;
+                }
+                double m0 = g, m1 = INFINITY;
+                wave_min2_f64(m0, m1);
+                if (m0 < best) {
+                    const int L = __ffsll((long long)__ballot(g == m0)) - 1;
+                    best = m0;
+                    bestT = bitsd(lane_u64(dbits(hT), L));
+                    bestE = bitsd(lane_u64(dbits(hE), L));
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const bool beaten = bestT < vT[r] && bestE < vE[r];
+                        vT[r] = beaten ? INFINITY : vT[r];
+                        vE[r] = beaten ? INFINITY : vE[r];
+                    }
+                }
+                uint64_t ms[R];
+                int tot = 0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    ms[r] = __ballot(vT[r] < INFINITY);
+                    tot += __popcll(ms[r]);
+                }
+                if (nb + tot > 64 && nb > 0) flush();
+                if (tot > 64) {  // more than the scratch holds
+                    tl = el = INFINITY;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        tl = vmin(tl, vT[r]);
+                        el = vmin(el, vE[r]);
+                    }
+                    count += wave_frontier<R>(vT, vE, tl, el, [&](int r) { return vI[r]; }, sc,
+                                              oT + count, oE + count, oI + count);
+                    ++parts;
+                    continue;
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (ms[r]) {
+                        if (vT[r] < INFINITY) {
+                            const int q = nb + lane_rank(ms[r]);
+                            sc.T[q] = vT[r];
+                            sc.E[q] = vE[r];
+                            sc.I[q] = vI[r];
+                        }
+                        nb += __popcll(ms[r]);
+                    }
             }
         }
+        if (nb > 0) flush();
         __syncthreads();  // every wave is done with the slab's tables
         const int ns = count - cs;
-        if (ns > 1 && ns <= scap) {
+        if (parts > 1 && ns > 1 && ns <= scap) {
             // this wave's own stores, complete after the wait: plain loads see them
             __builtin_amdgcn_s_waitcnt(KR_WAIT_VM0);
-            for (int x = lane; x < ns; x += 64) {
-                sT[x] = dbits(oT[cs + x]);
-                sE[x] = dbits(oE[cs + x]);
-                sI[x] = oI[cs + x];
+            if (ns <= 64) {  // one point per lane
+                const int x = cs + min(lane, ns - 1);
+                const double xT = oT[x], xE = oE[x];
+                const int32_t xI = oI[x];
+                const double v1T[1] = {lane < ns ? xT : INFINITY}, v1E[1] = {lane < ns ? xE : INFINITY};
+                count = cs + wave_frontier<1>(v1T, v1E, v1T[0], v1E[0], [&](int) { return xI; }, sc,
+                                              oT + cs, oE + cs, oI + cs);
+            } else {
+                for (int x = lane; x < ns; x += 64) {
+                    sT[x] = dbits(oT[cs + x]);
+                    sE[x] = dbits(oE[cs + x]);
+                    sI[x] = oI[cs + x];
+                }
+                wave_lds_fence();
+                wave_sort_keys(sT, sE, sI, ns);
+                count = cs + wave_frontier_scan(sT, sE, sI, ns, oT + cs, oE + cs, oI + cs);
             }
-            wave_lds_fence();
-            wave_sort_keys(sT, sE, sI, ns);
-            count = cs + wave_frontier_scan(sT, sE, sI, ns, oT + cs, oE + cs, oI + cs);
         }
         __syncthreads();  // the sort room is free again, and Lt, Lp may be overwritten
     }

@@ -63,3 +63,22 @@ def test_pruned_ties(oracle_lib, how):
             q = np.abs(tab[k]).max() / 8
             tab[k] = np.ceil(tab[k] / q) * q
     _check(oracle_lib, sp, tab)
+
+
+@pytest.mark.parametrize("pos", [2, 11, 24])
+@pytest.mark.parametrize("how", ["line", "ties"])
+def test_gathered_candidates(oracle_lib, how, pos):
+    """Candidates gather 64 to a frontier: slabs where none beats another (64 time-energy
+    trade-offs per launch position on one line, or equal energies throughout) fill the room,
+    overflow it and leave more frontiers than one."""
+    N = pos - 1
+    sp = I.Space(2, N, 2, pos, tuple(range(4, 12)), (1005.0, 1400.0), p_static=0.0)
+    tab = I.make_tables(sp, seed=3, comm_bytes=(8e6, 2e8))
+    tab["pw"][:] = 0.0
+    tab["pc"][:] = 0.0
+    if how == "line":
+        tab["t"][:] = 1e-3 * np.arange(1, N + 1)[:, None]
+        tab["tc"][:, :, 0] = 1.0 + np.arange(8) / 8
+        tab["tc"][:, :, 1] = 1.0 + np.arange(8) / 64
+        tab["pc"][:] = (3.0 - tab["tc"]) / tab["tc"]
+    _check(oracle_lib, sp, tab)
