@@ -461,9 +461,10 @@ kr_status kr_compare_frontiers(int64_t nA, const double *TA, const double *EA, i
  *                   KR_DP_CELL_CAP points, more than KR_DP_CAND candidates in a cell, or
  *                   more than KR_DP_ARENA points over all cells)
  *   status_out      device [1]: KR_OK, or KR_ECAPACITY if any instance hit a limit
- * Instances are first solved with a small on-chip budget (many per compute unit); the
- * few that need more are queued and solved again with half the full arena, and the
- * rest with the full budget.
+ * With overlap runs of at most 14 computations, instances are first solved four to a group
+ * with a small on-chip budget; the few that need more are queued and solved again, four to
+ * a group with a larger one, and the rest one at a time with the full budget.  Longer runs
+ * take the one-instance solver throughout: small budget, half the full arena, all of it.
  */
 #define KR_DP_MAX_OPS 24
 #define KR_DP_MAX_K 16

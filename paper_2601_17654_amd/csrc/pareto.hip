@@ -10,18 +10,18 @@
 // The union of a segment's unit frontiers is then sorted by a merge sort in LDS and
 // scanned: a 256-thread block per segment of up to 512 points, a 1024-thread block
 // for the few segments of up to 4096, and beyond that LDS-sized chunks whose
-// frontiers are merged pairwise in device memory.  A pairwise merge of two staircases
+// frontiers are merged pairwise in device memory; with up to KR_FUSED_SEGS segments one
+// launch does all of this and copies out (finalize_fused_kernel).  A pairwise merge of two staircases
 // needs no sort: an element's rank in the partner comes from a binary search, and it
 // survives iff the partner element just before it in key order has a larger E.
 #include "kr_filter.h"
 #include "kr_launch.h"
 
-
 namespace kr {
 
 // The layout kernels also clear lists[0], the count of segments that the first merge
-// stage passes on (or the ticket of the fused one), the segments' counts and the input check's verdict (so that neither needs a launch of its
-// own).
+// stage passes on (or the ticket of the fused one), the segments' counts and the input
+// check's verdict (so that none of them needs a launch of its own).
 __global__ void uniform_layout_kernel(int64_t *seg_off, int64_t *unit_base, int n_seg,
                                       int64_t seg_len, int64_t units_per_seg, int32_t *lists,
                                       int32_t *fcnt, int32_t *status)
