@@ -167,19 +167,21 @@ __device__ __forceinline__ double hvi_one(const double *fT, const double *fE, in
     return area + (end - start) * (level - e);
 }
 
-// Flat tiles of KR_HVI_TILE candidates; a tile visits every partition it overlaps.  Block 0
-// also turns the preparation's verdicts into the status word.
+// Flat tiles of KR_HVI_TILE candidates; a tile visits every partition it overlaps.  One block
+// more turns the preparation's verdicts into the status word and returns: a store ahead of the
+// tiles' uniform loads would take those off the scalar cache (138 M candidates: 956 us; with
+// block 0 doing both, 1,086).
 __global__ void __launch_bounds__(KR_BLOCK) hvi_score_kernel(HviArgs a)
 {
     __shared__ double fT[3][KR_HVI_MAX_OBS], fE[3][KR_HVI_MAX_OBS];
     const int tid = threadIdx.x;
-    if (blockIdx.x == 0) {
+    if (blockIdx.x == gridDim.x - 1) {
         bool bad = false;
         for (int g = tid; g < a.n_seg; g += KR_BLOCK) bad = bad || a.fr_n[g * 3] < 0;
         bad = __syncthreads_or(bad);
         if (tid == 0) *a.status = bad ? KR_EINVAL : KR_OK;
+        return;
     }
-    if (a.n_cand == 0) return;
     const int64_t t0 = (int64_t)blockIdx.x * KR_HVI_TILE;
     const int64_t t1 = t0 + KR_HVI_TILE < a.n_cand ? t0 + KR_HVI_TILE : a.n_cand;
     // last partition starting at or before t0 (uniform binary search)
@@ -246,8 +248,7 @@ hipError_t launch_hvi(const HviArgs &a, hipEvent_t *ev, hipStream_t st)
     hipLaunchKernelGGL(hvi_prep_kernel, dim3(a.n_seg, 3), dim3(KR_BLOCK), 0, st, a);
     const int64_t blocks = (a.n_cand + KR_HVI_TILE - 1) / KR_HVI_TILE;
     mark(ev, 0, st);
-    hipLaunchKernelGGL(hvi_score_kernel, dim3((unsigned)(blocks > 0 ? blocks : 1)), dim3(KR_BLOCK),
-                       0, st, a);
+    hipLaunchKernelGGL(hvi_score_kernel, dim3((unsigned)(blocks + 1)), dim3(KR_BLOCK), 0, st, a);
     mark(ev, 1, st);
     return hipGetLastError();
 }
