@@ -35,8 +35,8 @@
 // Of what is evaluated, most is beaten in time and energy by the wave's best candidate of the
 // slab so far (least E + mean power T); the rest gathers in the wave's scratch, 64 candidates to
 // a frontier, instead of taking a frontier per launch position (with the end of the first comm
-// phase tabled and a slab's frontiers merged one point per lane: 373 -> 279 us).  What is left
-// is latency: of those 279 us the sums, the table and the pruning take about 65, the
+// phase tabled and a slab's frontiers merged one point per lane: 373 -> 268 us).  What is left
+// is latency: of those 268 us the sums, the table and the pruning take about 65, the
 // positions' phases about 100.
 // A phase is kept as the values it adds to the energy sum and to the time, in the
 // order the walk adds them.  A candidate applies them to its own sums in that order,
@@ -565,7 +565,8 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
             ++parts;
         };
         // A chunk of R slots per position: the continuing candidate first, then rounds of kept
-        // pairs.  (Two positions sharing eight slots: 399 us, for the registers they take.)
+        // pairs.  Few slots, as few candidates are left to filter: R = 4 281 us, 3 281, 2 268, for
+        // the registers that more take.
         for (int p1 = 0; p1 < np; ++p1) {
             if (pair_owner(p1, NW) != wave) continue;
             const First o = first_phase(p1);
@@ -701,13 +702,13 @@ hipError_t launch_eval_filter_pair(const EvalArgs &a, const UnitOut &o, hipStrea
     constexpr int NW = KR_PAIR_WAVES;
     const dim3 grid(a.P * a.nfb), block(64 * NW);
     if (a.dma16 && a.S == 8 && a.N == 48 && a.n_pos == 33)
-        hipLaunchKernelGGL((eval_filter_pair_kernel<4, 16, NW, 8, true>), grid, block, lds, st, a, o);
+        hipLaunchKernelGGL((eval_filter_pair_kernel<2, 16, NW, 8, true>), grid, block, lds, st, a, o);
     else if (a.dma16 && a.S == 8)
-        hipLaunchKernelGGL((eval_filter_pair_kernel<4, 16, NW, 8, false>), grid, block, lds, st, a, o);
+        hipLaunchKernelGGL((eval_filter_pair_kernel<2, 16, NW, 8, false>), grid, block, lds, st, a, o);
     else if (a.dma16)
-        hipLaunchKernelGGL((eval_filter_pair_kernel<4, 16, NW, 0, false>), grid, block, lds, st, a, o);
+        hipLaunchKernelGGL((eval_filter_pair_kernel<2, 16, NW, 0, false>), grid, block, lds, st, a, o);
     else
-        hipLaunchKernelGGL((eval_filter_pair_kernel<4, 4, NW, 0, false>), grid, block, lds, st, a, o);
+        hipLaunchKernelGGL((eval_filter_pair_kernel<2, 4, NW, 0, false>), grid, block, lds, st, a, o);
     return hipGetLastError();
 }
 
