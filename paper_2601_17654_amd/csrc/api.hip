@@ -324,6 +324,7 @@ kr_status kr_pareto_filter(int64_t n_total, const double *T, const double *E,
     L.unit_base = w.unit_base;
     L.n_seg = n_seg;
     L.unit_stride = KR_TILE;
+    L.exact = true;
     const FrontierOut out{cap, out_off, out_idx, out_T, out_E};
     const bool raw = pareto_raw(n_total, n_seg);
     if ((n_seg > 0 || status_out) && !(raw && n_seg == 1) &&
@@ -389,6 +390,7 @@ kr_status kr_evaluate_and_filter(const kr_space *space, const double *t, const d
     L.unit_base = w.unit_base;
     L.n_seg = a.P;
     L.unit_stride = a.ustride;
+    L.exact = false;  // a unit holds a frontier per chunk or tile of each of its slabs
     return finish_segments(L, w, FrontierOut{cap, out_off, out_idx, out_T, out_E}, st);
 }
 
@@ -589,7 +591,7 @@ kr_status kr_microbatch_frontier(int32_t n_types, int32_t n_freq, const int64_t 
     a.slot_T = a.slot_E = nullptr;
     a.slot_choice = w.slot_choice;
     if (launch_mb_grid(a, w.g, st) != hipSuccess) return KR_EHIP;
-    const SegLayout L{w.f.seg_off, w.f.unit_base, 1, n_bins};
+    const SegLayout L{w.f.seg_off, w.f.unit_base, 1, n_bins, false};
     // an output never holds more points than there are slots
     const int64_t most = std::min(cap, (int64_t)n_freq * n_bins);
     const FrontierOut o{most, w.front_off, w.front_idx, out_T, out_E};

@@ -80,6 +80,7 @@ struct SegLayout {
     const int64_t *unit_base;  // [n_seg + 1]
     int n_seg;
     int64_t unit_stride;
+    bool exact;                // a unit's points are a frontier, in order (else any points)
 };
 
 struct PointBufs {

@@ -5,9 +5,11 @@
 // resolved to the smallest index.  The rule is decomposable: the frontier of a union
 // is the frontier of the union of the parts' frontiers.
 //
-// Work split: every segment is cut into units (tiles of points, or the frequency
-// range of one fused workgroup) whose exact frontiers are written to the unit's slot.
-// The union of a segment's unit frontiers is then sorted by a merge sort in LDS and
+// Work split: every segment is cut into units with a slot each.  A tile of points leaves
+// its exact frontier there (SegLayout::exact); the frequency range of a fused workgroup
+// leaves the frontiers of its chunks or tiles one behind another, and a frequency of a
+// microbatch its configurations, in no order that the merge relies on.
+// The union of a segment's units is then sorted by a merge sort in LDS and
 // scanned: a 256-thread block per segment of up to 512 points, a 1024-thread block
 // for the few segments of up to 4096, and beyond that LDS-sized chunks whose
 // frontiers are merged pairwise in device memory; with up to KR_FUSED_SEGS segments one
@@ -504,7 +506,7 @@ finalize_small_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs
     if (g == 0 && threadIdx.x == 0) lists[1] = 0;
     int n;
     const int64_t u0 = L.unit_base[g];
-    if (L.unit_base[g + 1] - u0 == 1) {  // one unit: its frontier is the segment's
+    if (L.exact && L.unit_base[g + 1] - u0 == 1) {  // one unit: its frontier is the segment's
         const int64_t s0 = L.seg_off[g];
         n = ucnt[u0];
         for (int64_t x = s0 + threadIdx.x; x < s0 + n; x += KR_FM_SMALL_NT) {
