@@ -419,7 +419,9 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
         __syncthreads();
         // Champions: per position the pair at it or later with the least Z + c X, for two
         // weights c around the slab's mean power (a time-leaning and an energy-leaning one).
-        // Testing every pair against these two keeps 9 of 264, against all of them 7.
+        // Testing every pair against these two keeps 9 of 264, against all of them 7.  A
+        // lane starts from its position's own first pair: where the sums overflow that one
+        // stays, and any pair at or after a position may stand there.
         const double mean = zall.a > 0.0 ? p_static + zall.b / zall.a : p_static;
         const double c0 = 0.25 * mean, c1 = 4.0 * mean;
         if (wave == 0) {
@@ -427,10 +429,11 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
             int a0 = 0, a1 = 0;
             for (int base = (np - 1) / 64 * 64; base >= 0; base -= 64) {
                 double g0 = INFINITY, g1 = INFINITY;
-                int i0 = 0, i1 = 0;
+                const int own = min(base + lane, np - 1) * S;
+                int i0 = own, i1 = own;
                 if (base + lane < np)
                     for (int c = 0; c < S; ++c) {
-                        const int q = (base + lane) * S + c;
+                        const int q = own + c;
                         const PairPart y = part[q];
                         const double v0 = y.z + c0 * y.x, v1 = y.z + c1 * y.x;
                         i0 = v0 < g0 ? q : i0;
