@@ -453,8 +453,8 @@ struct QuadShared {
 };
 
 // The instances of group `grp`: 4 * grp .. 4 * grp + 3 of all, or of the first queue; the
-// ones that need more (points than the pool holds, or more than 64 candidates in a cell; 128
-// from the queue) go on the first queue, or from there on the second.
+// ones that need more (points than the pool or KR_DP_ARENA holds, or more than 64 candidates in
+// a cell; 128 from the queue) go on the first queue, or from there on the second.
 template <bool QUEUED>
 __device__ __forceinline__ void dp_quad(const DpArgs &a, int64_t grp, int64_t n, int pool,
                                         char *lds, QuadShared &sh)
@@ -645,7 +645,17 @@ __device__ __forceinline__ void dp_quad(const DpArgs &a, int64_t grp, int64_t n,
     }
     __syncthreads();
     if (!there) return;
-    if (sh.dead >> row & 1) {
+    // The pool is shared, but the limit of KR_DP_ARENA points over all cells is an
+    // instance's own: with the pool above it the row counts its points (every wave its four
+    // rows alike), so that no verdict depends on the instances beside it.
+    dead = sh.dead >> row & 1;
+    if (sh.used > KR_DP_ARENA) {
+        int points = 0;
+        for (int x = r; x < ncell; x += 16) points += cell[x] & 0xFF;
+        for (int m = 8; m > 0; m >>= 1) points += __shfl_xor(points, m, 64);
+        dead = dead || points > KR_DP_ARENA;
+    }
+    if (dead) {
         if (wave == 0 && r == 0) {
             a.out_n[inst] = -1;
             int32_t *const queue = a.retry + (QUEUED ? a.n_inst : 0);
