@@ -213,7 +213,9 @@ size_t kr_evaluate_and_filter_workspace(const kr_space *space);
  *                                 more than B bins, KR_EINVAL for an empty partition, or
  *                                 KR_ENONFINITE for a non-finite time or an energy that
  *                                 is not a finite value >= 0 (then nothing else is
- *                                 meaningful and n_stair is 0)
+ *                                 meaningful and n_stair is 0), or KR_EHIP if a wait
+ *                                 between blocks was given up (only where two calls use
+ *                                 one workspace at the same time)
  */
 kr_status kr_compose_frontiers(int32_t n_parts, const int64_t *off, const double *T,
                                const double *E, int32_t n_bins, double delta, double *F_out,

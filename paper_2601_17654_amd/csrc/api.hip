@@ -223,6 +223,14 @@ bool eval_plan(const kr_space *s, bool fused, EvalArgs *a)
     return true;
 }
 
+// Most polls of a wait between blocks; a test-only switch lowers it, so that tests reach the
+// giving up.
+int wait_polls()
+{
+    const char *e = std::getenv("KR_TEST_WAIT_POLLS");
+    return e ? std::max(0, std::min(KR_WAIT_POLLS, std::atoi(e))) : KR_WAIT_POLLS;
+}
+
 // Caller-owned events recorded around a phase (kr_set_phase_events), one setting per
 // host thread: a call reads only its own thread's entries, so threads never race on them.
 thread_local hipEvent_t g_phase_ev[6][2] = {};
@@ -468,6 +476,7 @@ kr_status kr_compose_frontiers(int32_t n_parts, const int64_t *off, const double
     a.status = status_out;
     a.stair_Tlo = stair_Tlo;
     a.stair_E = stair_E;
+    a.polls = wait_polls();
     hipEvent_t *ev = g_phase_ev[KR_PHASE_MINPLUS];
     return launch_compose(a, w, ev[0] && ev[1] ? ev : nullptr, (hipStream_t)stream) == hipSuccess
                ? KR_OK

@@ -786,24 +786,28 @@ __device__ __forceinline__ T block_scan_excl(T v, T identity, Op op, T *lds, T *
 // bins.  It publishes its chunk's least value, takes the least of the chunks before it from
 // theirs, scans its bins, publishes its count of kept bins, and places them behind those of
 // the chunks before.  Chunks are handed out by ticket, so a block waits only for blocks that
-// started before it.  (Three launches, one per pass, cost 10 us and their gaps; the call on
-// 4 partitions and 1,024 bins is launches and nothing else.)  Thread t holds bins
-// 4t .. 4t + 3 of its chunk.
+// started before it; a wait of more than a.polls polls all the same (another call is using
+// this workspace) gives up with KR_EHIP.  (Three launches, one per pass, cost 10 us and their
+// gaps; the call on 4 partitions and 1,024 bins is launches and nothing else.)  Thread t holds
+// bins 4t .. 4t + 3 of its chunk.
 #define KR_ST_NT 256
 
 __global__ void __launch_bounds__(KR_ST_NT) staircase_kernel(ComposeArgs a, ComposeWs w)
 {
     __shared__ double sm[KR_ST_NT / 64];
     __shared__ int32_t si[KR_ST_NT / 64];
-    __shared__ int32_t s_chunk;
-    // a composition that failed (status set by an earlier kernel) has no staircase
-    if (*a.status != KR_OK) {
+    __shared__ int32_t s_chunk, s_lost;
+    if (threadIdx.x == 0) {
+        s_chunk = load_l2(a.status) == KR_OK ? atomicAdd(w.ticket + 1, 1) : -1;
+        s_lost = 0;
+    }
+    __syncthreads();
+    const int chunk = s_chunk;
+    // a composition that failed has no staircase; a ticket past the chunks is another call's
+    if (chunk < 0 || chunk >= (int)gridDim.x) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *a.n_stair = 0;
         return;
     }
-    if (threadIdx.x == 0) s_chunk = atomicAdd(w.ticket + 1, 1);
-    __syncthreads();
-    const int chunk = s_chunk;
     const int b0 = chunk * KR_ST_CHUNK + 4 * threadIdx.x;
     double v[4], tm = INFINITY;
 #pragma unroll
@@ -811,13 +815,24 @@ __global__ void __launch_bounds__(KR_ST_NT) staircase_kernel(ComposeArgs a, Comp
         v[q] = b0 + q < a.B ? a.F_out[b0 + q] : INFINITY;
         tm = MinF64()(tm, v[q]);
     }
+    // *p once it is not `unset` (then true)
+    auto fetch = [&](const auto *p, auto unset, auto &x) {
+        for (int n = 0; (x = load_l2(p)) == unset; ++n) {
+            if (n >= a.polls) {
+                s_lost = 1;
+                return false;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        return true;
+    };
     double least;
     double run = block_scan_excl<KR_ST_NT>(tm, (double)INFINITY, MinF64(), sm, &least);
     if (threadIdx.x == 0) store_dev((uint64_t *)w.chmin + chunk, dbits(least));
     double before = INFINITY;
     for (int c = threadIdx.x; c < chunk; c += KR_ST_NT) {
         uint64_t x;
-        while ((x = load_l2((const uint64_t *)w.chmin + c)) == KR_UNSET) __builtin_amdgcn_s_sleep(1);
+        if (!fetch((const uint64_t *)w.chmin + c, (uint64_t)KR_UNSET, x)) break;
         before = MinF64()(before, bitsd(x));
     }
     double tot;
@@ -836,11 +851,17 @@ __global__ void __launch_bounds__(KR_ST_NT) staircase_kernel(ComposeArgs a, Comp
     int32_t earlier = 0;
     for (int c = threadIdx.x; c < chunk; c += KR_ST_NT) {
         int32_t x;
-        while ((x = load_l2(w.chcnt + c)) < 0) __builtin_amdgcn_s_sleep(1);
-        earlier += x;
+        if (!fetch(w.chcnt + c, (int32_t)-1, x)) break;
+        earlier += min(max(x, 0), KR_ST_CHUNK);
     }
     int32_t first;
     block_scan_excl<KR_ST_NT>(earlier, 0, SumI32(), si, &first);
+    const bool lost = s_lost != 0, last = chunk == (int)gridDim.x - 1;
+    if (lost) {
+        if (threadIdx.x == 0) store_dev(a.status, (int32_t)KR_EHIP);
+        if (last && threadIdx.x == 0) *a.n_stair = 0;
+        return;
+    }
     pos += first;
     const double delta = a.info[0], tmin_sum = a.info[1];
 #pragma unroll
@@ -851,7 +872,7 @@ __global__ void __launch_bounds__(KR_ST_NT) staircase_kernel(ComposeArgs a, Comp
             a.stair_E[pos] = v[q];
             ++pos;
         }
-    if (chunk == (int)gridDim.x - 1 && threadIdx.x == 0) *a.n_stair = first + n;
+    if (last && threadIdx.x == 0) *a.n_stair = load_l2(a.status) == KR_OK ? first + n : 0;
 }
 
 hipError_t launch_compose(const ComposeArgs &a, const ComposeWs &w, hipEvent_t *minplus_ev,

@@ -10,6 +10,9 @@
 #define KR_PAIR_WAVES 4    // waves per block of the two-comm evaluation kernel
 #define KR_FIN_UNITS 2048  // units per segment the finalize kernel's LDS path takes
 #define KR_TILE 2048       // points per tile of the stand-alone filter
+// Polls after which a block stops waiting for one that started before it (seconds).  Waits
+// end by themselves unless two calls use one workspace at the same time.
+#define KR_WAIT_POLLS (1 << 24)
 // Positions per chunk that the wave kernel is compiled for.  Runs of 1 to 8 positions get
 // their own size, longer ones waste one round at most (three above 14).
 #define KR_WAVE_R 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 17
@@ -159,6 +162,7 @@ struct ComposeArgs {
     double *info;
     int32_t *L_out, *stair_bin, *n_stair, *status;
     double *stair_Tlo, *stair_E;
+    int polls;              // most polls of a wait inside the staircase
 };
 hipError_t launch_compose(const ComposeArgs &a, const ComposeWs &w, hipEvent_t *minplus_ev,
                           hipStream_t st);
