@@ -37,6 +37,8 @@
  *    status word (status_out, NULL to skip): when given, every input value is checked
  *    where the kernels read it and the word receives KR_OK, or KR_ENONFINITE if some
  *    value is NaN, infinite or negative.  kr_compose_frontiers always checks its points.
+ *    (KR_EHIP there says that a wait between blocks was given up, which takes two calls
+ *    that use one workspace at the same time; their other outputs are unspecified.)
  *    With invalid inputs the other outputs are unspecified but memory-safe.
  */
 #ifndef KAREUS_H

@@ -333,7 +333,7 @@ kr_status kr_pareto_filter(int64_t n_total, const double *T, const double *E,
     L.n_seg = n_seg;
     L.unit_stride = KR_TILE;
     L.exact = true;
-    const FrontierOut out{cap, out_off, out_idx, out_T, out_E};
+    const FrontierOut out{cap, out_off, out_idx, out_T, out_E, status_out, wait_polls()};
     const bool raw = pareto_raw(n_total, n_seg);
     if ((n_seg > 0 || status_out) && !(raw && n_seg == 1) &&
         launch_tile_layout(seg_off, w.unit_base, n_seg, KR_TILE, w.lists, w.fcnt, status_out, st) !=
@@ -341,7 +341,7 @@ kr_status kr_pareto_filter(int64_t n_total, const double *T, const double *E,
         return KR_EHIP;
     if (raw) {
         phase_mark(KR_PHASE_MERGE, 0, st);
-        if (launch_pareto_raw(T, E, n_total, L, w.fcnt, w.lists, out, status_out, st) != hipSuccess)
+        if (launch_pareto_raw(T, E, n_total, L, w.fcnt, w.lists, out, st) != hipSuccess)
             return KR_EHIP;
         phase_mark(KR_PHASE_MERGE, 1, st);
         return KR_OK;
@@ -399,7 +399,8 @@ kr_status kr_evaluate_and_filter(const kr_space *space, const double *t, const d
     L.n_seg = a.P;
     L.unit_stride = a.ustride;
     L.exact = false;  // a unit holds a frontier per chunk or tile of each of its slabs
-    return finish_segments(L, w, FrontierOut{cap, out_off, out_idx, out_T, out_E}, st);
+    const FrontierOut out{cap, out_off, out_idx, out_T, out_E, status_out, wait_polls()};
+    return finish_segments(L, w, out, st);
 }
 
 size_t kr_compose_frontiers_workspace(int32_t n_parts, int32_t n_bins)
@@ -603,7 +604,7 @@ kr_status kr_microbatch_frontier(int32_t n_types, int32_t n_freq, const int64_t 
     const SegLayout L{w.f.seg_off, w.f.unit_base, 1, n_bins, false};
     // an output never holds more points than there are slots
     const int64_t most = std::min(cap, (int64_t)n_freq * n_bins);
-    const FrontierOut o{most, w.front_off, w.front_idx, out_T, out_E};
+    const FrontierOut o{most, w.front_off, w.front_idx, out_T, out_E, nullptr, 0};
     const kr_status rc = finish_segments(L, w.f, o, st);
     if (rc != KR_OK) return rc;
     return launch_mb_gather(a, w.front_off, w.front_idx, cap, out_f, out_choice, n_out, st) ==

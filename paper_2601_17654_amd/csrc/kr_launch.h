@@ -113,12 +113,15 @@ hipError_t launch_tile_layout(const int64_t *seg_off, int64_t *unit_base, int n_
 hipError_t launch_pareto_tiles(const double *T, const double *E, const SegLayout &L,
                                int64_t n_units_bound, const UnitOut &o, int32_t *status,
                                hipStream_t st);
-// CSR output of a filter: offsets [n_seg + 1], points up to element cap.
+// CSR output of a filter: offsets [n_seg + 1], points up to element cap; the status word of
+// the call or NULL, and the most polls of a wait between blocks.
 struct FrontierOut {
     int64_t cap;
     int64_t *off;
     int32_t *idx;
     double *T, *E;
+    int32_t *status;
+    int polls;
 };
 // Union of every segment's unit frontiers.  lists: 2 * n_seg + 2 ints of scratch; lists[0]
 // and fcnt[n_seg] zero on entry (cleared by the layout launches above; a single segment
@@ -127,11 +130,10 @@ hipError_t launch_merge(const SegLayout &L, const PointBufs &buf, const int32_t 
                         const PointBufs &fin, int32_t *fcnt, int32_t *runcnt, uint8_t *flags,
                         int32_t *lists, const FrontierOut &o, hipStream_t st);
 // Whether the points are few enough for one launch that sorts each segment in LDS, and that
-// launch (lists, fcnt as above; with several segments *status KR_OK on entry).
+// launch (lists, fcnt as above; with several segments the status word KR_OK on entry).
 bool pareto_raw(int64_t n_total, int n_seg);
 hipError_t launch_pareto_raw(const double *T, const double *E, int64_t n_total, const SegLayout &L,
-                             int32_t *fcnt, int32_t *lists, const FrontierOut &o, int32_t *status,
-                             hipStream_t st);
+                             int32_t *fcnt, int32_t *lists, const FrontierOut &o, hipStream_t st);
 
 // compose.hip
 struct ComposeWs {

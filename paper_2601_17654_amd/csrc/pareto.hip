@@ -195,15 +195,17 @@ __device__ __forceinline__ int rank_in(const double *bT, const double *bE, const
 }
 
 // Merge staircases a = in[sa, sa+na) and b = in[sb, sb+nb) into out[sa ...); returns
-// the merged frontier's size.  Every thread of the block must call.
-template <int NT>
+// the merged frontier's size.  Every thread of the block must call.  beat() is called every
+// now and then (see finalize_fused_kernel).
+template <int NT, typename Beat>
 __device__ inline int merge_pair(const PointBufs &in, const PointBufs &out, uint8_t *flags,
-                                 int64_t sa, int na, int64_t sb, int nb)
+                                 int64_t sa, int na, int64_t sb, int nb, const Beat &beat)
 {
     __shared__ int32_t sc[NT / 64];
     const double *aT = in.T + sa, *aE = in.E + sa, *bT = in.T + sb, *bE = in.E + sb;
     const int32_t *aI = in.I + sa, *bI = in.I + sb;
     for (int x = threadIdx.x; x < na + nb; x += NT) {
+        if (x / NT % 256 == 0) beat();
         const bool fromA = x < na;
         const int y = fromA ? x : x - na;
         const double t = ld_l2(fromA ? aT + y : bT + y);
@@ -223,6 +225,7 @@ __device__ inline int merge_pair(const PointBufs &in, const PointBufs &out, uint
     const int n = na + nb;
     int base = 0;
     for (int c0 = 0; c0 < n; c0 += NT) {
+        if (c0 / NT % 256 == 0) beat();
         const int x = c0 + threadIdx.x;
         const bool has = x < n;
         double t = 0.0, e = 0.0;
@@ -541,10 +544,10 @@ finalize_large_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs
 // Stage 3, the segments on the second list: one block per segment (blocks loop over
 // the list), returning the frontier's size.  The union is sorted in LDS when it fits; otherwise it is cut into
 // LDS-sized chunks whose frontiers are merged pairwise in device memory.
-template <int NT>
+template <int NT, typename Beat>
 __device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs &buf,
                                       const int32_t *ucnt, const PointBufs &fin, int32_t *runcnt,
-                                      uint8_t *flags, FinLds &sh, int32_t *sc)
+                                      uint8_t *flags, FinLds &sh, int32_t *sc, const Beat &beat)
 {
     const int64_t s0 = L.seg_off[g];
     const int64_t u0 = L.unit_base[g];
@@ -599,6 +602,7 @@ __device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs
     int32_t *rc = runcnt + s0 / KR_FIN_CAP + g;
     const int nchunks = (int)((total + KR_FIN_CAP - 1) / KR_FIN_CAP);
     for (int c = 0; c < nchunks; ++c) {
+        beat();
         const int64_t c0 = (int64_t)c * KR_FIN_CAP;
         const int n = (int)min((int64_t)KR_FIN_CAP, total - c0);
         for (int x = threadIdx.x; x < n; x += NT) {
@@ -621,7 +625,8 @@ __device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs
             int merged;
             if (r + span < nchunks) {
                 const int64_t sb = s0 + (int64_t)(r + span) * KR_FIN_CAP;
-                merged = merge_pair<NT>(cur, other, flags, sa, na, sb, ld_l2(rc + r + span));
+                merged = merge_pair<NT>(cur, other, flags, sa, na, sb, ld_l2(rc + r + span),
+                                        beat);
             } else {
                 for (int x = threadIdx.x; x < na; x += NT) {
                     other.T[sa + x] = ld_l2(cur.T + sa + x);
@@ -658,7 +663,8 @@ finalize_block_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs
     const int cnt = lists[1];
     for (int i = blockIdx.x; i < cnt; i += gridDim.x) {
         const int g = lists[2 + L.n_seg + i];
-        const int n = finalize_block_segment<KR_BLOCK>(g, L, buf, ucnt, fin, runcnt, flags, sh, sc);
+        const int n = finalize_block_segment<KR_BLOCK>(g, L, buf, ucnt, fin, runcnt, flags, sh, sc,
+                                                       [] {});
         if (threadIdx.x == 0) fcnt[g] = n;
         __syncthreads();  // LDS reuse by the next segment
     }
@@ -669,7 +675,12 @@ finalize_block_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs
 // threads each, which then fit on the chip together): a block merges its segment in LDS, or
 // in chunks when it is larger, publishes its count, and writes the frontier to its final
 // place as soon as the counts before it are known.  Blocks take their segments by ticket, so
-// a block waits only for segments of blocks that started before it.  Four launches of which
+// a block waits only for segments of blocks that started before it.  Waits are bounded all the
+// same, for two calls that use one workspace at the same time: a count that neither comes nor
+// changes for o.polls polls is given up, the block writes nothing, and the status word (if
+// there is one) says KR_EHIP.  fcnt[g] is 0 until segment g's block has its count (then
+// count + 1); a block that merges in chunks, which can take seconds, counts down from 0
+// meanwhile, so that the others see it at work.  Four launches of which
 // most blocks do nothing cost more than the merge itself where segments are few (4 to 256
 // partitions; the 1,518 configurations of a microbatch: 193 us a call, 126 us so).
 // RAW: the points come straight from (T, E), with no unit frontiers before (all segments
@@ -681,8 +692,7 @@ template <bool RAW>
 __global__ void __launch_bounds__(KR_FM_LARGE_NT)
 finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayout L,
                       PointBufs buf, const int32_t *ucnt, PointBufs fin, int32_t *fcnt,
-                      int32_t *runcnt, uint8_t *flags, int32_t *lists, FrontierOut o,
-                      int32_t *status)
+                      int32_t *runcnt, uint8_t *flags, int32_t *lists, FrontierOut o)
 {
     constexpr int NT = KR_FM_LARGE_NT, PER = KR_FM_LARGE_PER;
     union Lds {
@@ -691,7 +701,8 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
         __device__ Lds() {}
     };
     __shared__ Lds sh;
-    __shared__ int32_t s_seg;
+    __shared__ int32_t s_seg, s_beats;
+    __shared__ int32_t *s_beat;
     __shared__ int32_t sc32[NT / 64];
     __shared__ int64_t sc64[NT / 64];
     const int tid = threadIdx.x;
@@ -700,8 +711,21 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
         if (tid == 0) s_seg = atomicAdd(&lists[0], 1);
         __syncthreads();
         g = s_seg;
+        if (g < 0 || g >= L.n_seg) return;  // another call's ticket
     }
-    // the first output element of segment g, which holds `count` points
+    // The beat's place and number wait in LDS: the kernel has no scalar register to spare (1 M
+    // points in one segment took 2.5 % longer with them there).
+    if (!RAW && tid == 0) {
+        s_beat = L.n_seg > 1 ? fcnt + g : nullptr;
+        s_beats = 0;
+    }
+    auto beat = [&] {
+        if (threadIdx.x == 0 && s_beat)
+            __hip_atomic_store(s_beat, --s_beats, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    // the first output element of segment g, which holds `count` points (cap: a wait was given
+    // up).  A count given up makes the sum of up to KR_FUSED_SEGS counts negative.
+    constexpr int64_t kLost = -((int64_t)1 << 50);
     auto place = [&](int count) -> int64_t {
         int64_t d0 = 0;
         if (L.n_seg > 1) {
@@ -710,11 +734,25 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
                 __hip_atomic_store(fcnt + g, count + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             int64_t before = 0;
             if (tid < g) {
-                int32_t c;
-                while ((c = ld_l2(fcnt + tid)) == 0) __builtin_amdgcn_s_sleep(1);
-                before = c - 1;
+                int32_t c, seen = 0;
+                for (int n = 0; (c = ld_l2(fcnt + tid)) <= 0;) {
+                    if (c != seen) n = 0;
+                    else if (++n > o.polls) break;
+                    seen = c;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                before = c > 0 ? c - 1 : kLost;
             }
             d0 = block_reduce<int64_t, SumI64, NT / 64>(before, (int64_t)0, SumI64(), sc64);
+            if (d0 < 0) {
+                if (tid == 0) {
+                    if (o.status) __hip_atomic_store(o.status, (int32_t)KR_EHIP, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+                    o.off[g] = 0;
+                    if (g == L.n_seg - 1) o.off[L.n_seg] = 0;
+                }
+                return o.cap;
+            }
         }
         if (tid == 0) {
             o.off[g] = d0;
@@ -737,12 +775,12 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
                 }
         };
         merge_segment(n, points, sh.merge, o.T, o.E, o.idx, o.cap, place);
-        if (status) {
+        if (o.status) {
             if (L.n_seg > 1) {
-                report_values(status, worst >= KR_BAD_HI);  // KR_OK before the launch
+                report_values(o.status, worst >= KR_BAD_HI);  // KR_OK before the launch
             } else {
                 const int bad = __syncthreads_or(worst >= KR_BAD_HI);
-                if (tid == 0) *status = bad ? KR_ENONFINITE : KR_OK;
+                if (tid == 0) *o.status = bad ? KR_ENONFINITE : KR_OK;
             }
         }
         return;
@@ -755,7 +793,7 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
         return;
     }
     __syncthreads();
-    n = finalize_block_segment<NT>(g, L, buf, ucnt, fin, runcnt, flags, sh.fin, sc32);
+    n = finalize_block_segment<NT>(g, L, buf, ucnt, fin, runcnt, flags, sh.fin, sc32, beat);
     __syncthreads();  // the block's stores to fin are read back below
     const int64_t d0 = place(n), src0 = L.seg_off[g];
     for (int64_t x = tid; x < n && d0 + x < o.cap; x += NT) {
@@ -771,13 +809,12 @@ bool pareto_raw(int64_t n_total, int n_seg)
 }
 
 hipError_t launch_pareto_raw(const double *T, const double *E, int64_t n_total, const SegLayout &L,
-                             int32_t *fcnt, int32_t *lists, const FrontierOut &o, int32_t *status,
-                             hipStream_t st)
+                             int32_t *fcnt, int32_t *lists, const FrontierOut &o, hipStream_t st)
 {
     const PointBufs none{nullptr, nullptr, nullptr};
     hipLaunchKernelGGL(finalize_fused_kernel<true>, dim3(L.n_seg), dim3(KR_FM_LARGE_NT), 0, st, T,
                        E, n_total, L, none, (const int32_t *)nullptr, none, fcnt,
-                       (int32_t *)nullptr, (uint8_t *)nullptr, lists, o, status);
+                       (int32_t *)nullptr, (uint8_t *)nullptr, lists, o);
     return hipGetLastError();
 }
 
@@ -881,7 +918,7 @@ hipError_t launch_merge(const SegLayout &L, const PointBufs &buf, const int32_t 
     if (L.n_seg >= 1 && L.n_seg <= KR_FUSED_SEGS) {
         hipLaunchKernelGGL(finalize_fused_kernel<false>, dim3(L.n_seg), dim3(KR_FM_LARGE_NT), 0, st,
                            (const double *)nullptr, (const double *)nullptr, (int64_t)0, L, buf,
-                           ucnt, fin, fcnt, runcnt, flags, lists, o, (int32_t *)nullptr);
+                           ucnt, fin, fcnt, runcnt, flags, lists, o);
         return hipGetLastError();
     }
     const hipError_t e = launch_finalize(L, buf, ucnt, fin, fcnt, runcnt, flags, lists, st);
