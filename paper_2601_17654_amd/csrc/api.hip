@@ -104,6 +104,7 @@ bool wave_plan(EvalArgs *a)
     // a few times more one-wave blocks than fit on the chip at once, so the
     // dispatcher balances uneven slabs; within a block slab copies overlap the filter
     const int64_t resident = std::max<int64_t>(1, std::min<int64_t>(16, kLdsPerCu / (lds * 8)));
+    a->four = resident >= 16;
     const int64_t target = kWaveBlocksPerSlot * 256 * resident;
     int64_t nfb = std::max<int64_t>(1, (target + a->P - 1) / a->P);
     nfb = std::min<int64_t>(nfb, a->F);

@@ -88,17 +88,9 @@ __device__ __forceinline__ void finish_tail(const Tail &q, double p_static, doub
 // 32 SM choices: runs of 16 and 17 positions) makes the sizes and LDS offsets
 // immediates and lets every round but the last skip the validity selects.
 //
-// The registers decide how many waves share a SIMD, and a wave alone leaves it idle most of
-// the time.  Held to three waves, chunks of 10 to 14 took 214 us instead of 232 (14) and 120
-// instead of 135 (10); held to four, chunks of 4 to 8 took 99 instead of 106 (5) and 23.5
-// instead of 25.2 (7).  Chunks of 3 lost by four (143 against 135), and 17 are bound by LDS.
-constexpr int wave_occupancy(int R, int W)
-{
-    return R >= 4 && R <= 8 && W == 16 ? 4 : R >= 10 && R <= 14 ? 3 : 1;
-}
-
-template <int R, int W, int SC, bool FX>
-__global__ void __launch_bounds__(64, wave_occupancy(R, W)) eval_filter_wave_kernel(EvalArgs a, UnitOut o)
+// OCC: waves per SIMD that the registers are held to (1: not held), see launch_eval_filter_wave.
+template <int R, int W, int SC, bool FX, int OCC>
+__global__ void __launch_bounds__(64, OCC) eval_filter_wave_kernel(EvalArgs a, UnitOut o)
 {
     constexpr int K = KR_PAD;
     extern __shared__ double lds[];
@@ -349,29 +341,51 @@ __global__ void __launch_bounds__(64, wave_occupancy(R, W)) eval_filter_wave_ker
     if (lane == 0) o.cnt[blockIdx.x] = count;
 }
 
-template <int R, int SC, bool FX = false>
+template <int R, int SC, bool FX = false, int OCC16 = 1>
 static void launch_wave_r(const EvalArgs &a, const UnitOut &o, size_t lds, hipStream_t st)
 {
+    constexpr int OCC = R >= 10 && R <= 14 ? 3 : 1;
     const dim3 grid(a.P * a.nfb), block(64);
-    if (a.dma16)
-        hipLaunchKernelGGL((eval_filter_wave_kernel<R, 16, SC, FX>), grid, block, lds, st, a, o);
+    if (a.dma16 && OCC16 > 1 && a.four)
+        hipLaunchKernelGGL((eval_filter_wave_kernel<R, 16, SC, FX, OCC16>), grid, block, lds, st, a, o);
+    else if (a.dma16)
+        hipLaunchKernelGGL((eval_filter_wave_kernel<R, 16, SC, FX, OCC>), grid, block, lds, st, a, o);
     else
-        hipLaunchKernelGGL((eval_filter_wave_kernel<R, 4, SC, FX>), grid, block, lds, st, a, o);
+        hipLaunchKernelGGL((eval_filter_wave_kernel<R, 4, SC, FX, OCC>), grid, block, lds, st, a, o);
 }
 
 // The general instance of a.R positions per chunk; false if it is none of Rs.
 template <int... Rs>
 static bool launch_wave_any(const EvalArgs &a, const UnitOut &o, size_t lds, hipStream_t st)
 {
-    return ((a.R == Rs && (launch_wave_r<Rs, 0>(a, o, lds, st), true)) || ...);
+    return ((a.R == Rs &&
+             (launch_wave_r<Rs, 0, false, Rs >= 4 && Rs <= 6 ? 4 : 1>(a, o, lds, st), true)) || ...);
 }
 
+// Instances.  256 partitions x 64 frequencies, kernel time in us, "a -> b" the general or free
+// one against the one taken:
+//  - Registers held to four waves per SIMD (some spill) where LDS lets four share one (a.four),
+//    for chunks of 4 to 6 (16 SM choices: 63.0 -> 59.8, 67.5 -> 65.0, 73.0 -> 69.5; 8: 65.1 ->
+//    60.3, 73.3 -> 69.0, 84.6 -> 79.6) and, with the SM choices fixed, 7 and 8 (71.3 -> 67.2,
+//    80.5 -> 75.0).  General chunks of 7 and 8 spill too much for it (77.3 -> 78.0, 85.5 ->
+//    84.9), and where LDS lets fewer waves share a SIMD only the spills are left: 32 SM choices,
+//    16 positions 96 -> 112, 8 SM choices, 80 kernels, 54 positions 119 -> 132.
+//  - Registers held to three for chunks of 10 to 14 (20 SM choices, 42 kernels: 130 -> 124,
+//    142.5 -> 139.5, 154.5 -> 151; 18 SM choices, 14 to a chunk, 8-byte slabs: 161 -> 138).
+//    Chunks of 1 to 3 lose by it.  17 take 204 registers, two waves, and on the largest slabs
+//    LDS takes no more.
+//  - 8 or 16 SM choices, chunks of 7 and 8: with the row offsets immediates the kernel keeps more
+//    in registers (16 choices: 77.4 -> 71.4, 85.1 -> 80.1; 8: 97.1 -> 90.7, 102 -> 95.5).
+//  - 32 SM choices, chunks of 17, and that with everything fixed: see above.
 hipError_t launch_eval_filter_wave(const EvalArgs &a, const UnitOut &o, hipStream_t st)
 {
     const size_t lds = (size_t)a.lds_doubles * sizeof(double);
     if (a.S == 32 && a.R == 17 && a.fixed32) launch_wave_r<17, 32, true>(a, o, lds, st);
     else if (a.S == 32 && a.R == 17) launch_wave_r<17, 32>(a, o, lds, st);
-    else if (a.S == 16 && a.R == 7) launch_wave_r<7, 16>(a, o, lds, st);
+    else if (a.S == 16 && a.R == 7) launch_wave_r<7, 16, false, 4>(a, o, lds, st);
+    else if (a.S == 16 && a.R == 8) launch_wave_r<8, 16, false, 4>(a, o, lds, st);
+    else if (a.S == 8 && a.R == 7) launch_wave_r<7, 8, false, 4>(a, o, lds, st);
+    else if (a.S == 8 && a.R == 8) launch_wave_r<8, 8, false, 4>(a, o, lds, st);
     else if (!launch_wave_any<KR_WAVE_R>(a, o, lds, st)) return hipErrorInvalidValue;
     return hipGetLastError();
 }

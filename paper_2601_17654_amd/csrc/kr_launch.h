@@ -46,6 +46,7 @@ struct EvalArgs {
     int w_pw, w_a0;         // LDS offsets (doubles) of the power slab and the column sums
     int dma16;              // 16-byte direct copies (slab length even, tables 16-byte aligned)
     int wcap;               // candidates the wave filter's LDS scratch holds
+    int four;               // LDS lets four waves share a SIMD
     // 32 kernels, 33 launch positions and 32 SM choices (the evaluation stress shape):
     // two runs of 16 and 17 positions per SM choice, one chunk each.  The kernel instance
     // for it takes the sizes, the LDS layout and the validity of all but the last round
