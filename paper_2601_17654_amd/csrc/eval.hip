@@ -332,7 +332,7 @@ struct Prefetch {
         }
     }
 
-    // `worst`: the largest high word stored so far (input check)
+    // `worst`: the largest high word stored so far (input check, with a status word only)
     __device__ __forceinline__ void store(const EvalArgs &a, double *lds, uint32_t &worst) const
     {
         const int slab = a.N * (a.S + 1), ms = a.M * a.S;
@@ -340,14 +340,14 @@ struct Prefetch {
         for (int k = 0; k < PFT; ++k) {
             const int x = threadIdx.x + k * KR_BLOCK;
             if (x < slab) {
-                worst = max(worst, max(value_hi(t[k]), value_hi(pw[k])));
+                if (a.status) worst = max(worst, max(value_hi(t[k]), value_hi(pw[k])));
                 lds[x] = t[k];
                 lds[slab + x] = pw[k];
             }
         }
         const int x = threadIdx.x;
         if (x < ms) {
-            worst = max(worst, max(value_hi(c[0]), value_hi(c[1])));
+            if (a.status) worst = max(worst, max(value_hi(c[0]), value_hi(c[1])));
             lds[2 * slab + x] = c[0];
             lds[2 * slab + ms + x] = c[1];
         }

@@ -562,8 +562,8 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
             const int32_t xI = sc.I[x];
             const double fT[1] = {lane < nb ? xT : INFINITY}, fE[1] = {lane < nb ? xE : INFINITY};
             wave_lds_fence();
-            count += wave_frontier<1>(fT, fE, fT[0], fE[0], [&](int) { return xI; }, sc, oT + count,
-                                      oE + count, oI + count);
+            count += wave_frontier<1>(fT, fE, fT[0], fE[0], any_index([&](int) { return xI; }), sc,
+                                      oT + count, oE + count, oI + count);
             nb = 0;
             ++parts;
         };
@@ -649,7 +649,8 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
                         tl = vmin(tl, vT[r]);
                         el = vmin(el, vE[r]);
                     }
-                    count += wave_frontier<R>(vT, vE, tl, el, [&](int r) { return vI[r]; }, sc,
+                    count += wave_frontier<R>(vT, vE, tl, el,
+                                              any_index([&](int r) { return vI[r]; }), sc,
                                               oT + count, oE + count, oI + count);
                     ++parts;
                     continue;
@@ -678,8 +679,9 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
                 const double xT = oT[x], xE = oE[x];
                 const int32_t xI = oI[x];
                 const double v1T[1] = {lane < ns ? xT : INFINITY}, v1E[1] = {lane < ns ? xE : INFINITY};
-                count = cs + wave_frontier<1>(v1T, v1E, v1T[0], v1E[0], [&](int) { return xI; }, sc,
-                                              oT + cs, oE + cs, oI + cs);
+                count = cs + wave_frontier<1>(v1T, v1E, v1T[0], v1E[0],
+                                              any_index([&](int) { return xI; }), sc, oT + cs,
+                                              oE + cs, oI + cs);
             } else {
                 for (int x = lane; x < ns; x += 64) {
                     sT[x] = dbits(oT[cs + x]);

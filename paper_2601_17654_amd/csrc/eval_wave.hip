@@ -142,7 +142,7 @@ __global__ void __launch_bounds__(64, OCC) eval_filter_wave_kernel(EvalArgs a, U
         wave_lds_fence();
         const double tcm = tc_next, pc_cur = pc_next;
         const double ctail = pc_cur * tcm;
-        uint32_t worst = max(raw_hi(tcm), raw_hi(pc_cur));  // input check
+        uint32_t worst = a.status ? max(raw_hi(tcm), raw_hi(pc_cur)) : 0;  // input check
 
         // Running sums, 8 rows at a time: every lane sums its column (lane 0 the all-SM
         // column, writing the records; the others their comm-time column) and keeps the
@@ -168,9 +168,13 @@ __global__ void __launch_bounds__(64, OCC) eval_filter_wave_kernel(EvalArgs a, U
                         vw[q] = i0 + q < N ? bw[q * S1] : 0.0;
                     }
                 }
+                if (a.status) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        worst = max(worst, max(raw_hi(vt[q]), raw_hi(vw[q])));
+                }
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
-                    worst = max(worst, max(raw_hi(vt[q]), raw_hi(vw[q])));
                     ra[q] = sa;
                     rb[q] = sb;
                     sa = sa + vt[q];  // rows past N add +0: exact
@@ -209,8 +213,9 @@ __global__ void __launch_bounds__(64, OCC) eval_filter_wave_kernel(EvalArgs a, U
         // Input check: the sums read every value of the slab (each lane its column, lane 0
         // the all-SM one; with 64 SM choices no lane is left for column 1).  A raw high
         // word at KR_BAD_HI or above is a bad value or -0.0: the slab is looked at again.
-        // The one maximum per row cost nothing that could be measured.
-        if (SC == 0 && S == 64)
+        // One maximum per row; calls without a status word branch past it (138 M candidates:
+        // 920 us with the maxima always taken, 905 so, 911 with a status word).
+        if (SC == 0 && S == 64 && a.status)
             for (int i = lane; i < N; i += 64)
                 worst = max(worst, max(raw_hi(Lt[i * S1 + 1]), raw_hi(Lp[i * S1 + 1])));
         if (a.status && __ballot(worst >= KR_BAD_HI)) {
@@ -333,8 +338,7 @@ __global__ void __launch_bounds__(64, OCC) eval_filter_wave_kernel(EvalArgs a, U
                 tc_next = a.tc[pn * S + s];
                 pc_next = a.pc[pn * S + s];
             }
-            const int ibase = f * a.Cf + c0 * S + s;
-            count += wave_frontier<R>(vT, vE, tl, el, [&](int r) { return ibase + r * S; }, sc,
+            count += wave_frontier<R>(vT, vE, tl, el, StepIndex{f * a.Cf + c0 * S + s, S}, sc,
                                       oT + count, oE + count, oI + count);
         }
     }

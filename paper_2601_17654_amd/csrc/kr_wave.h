@@ -106,6 +106,28 @@ __device__ __forceinline__ void emit(const Key &k, int n, double *oT, double *oE
     }
 }
 
+// Candidate indices of the lanes' slots: index(r) is this lane's slot r, index.of(r, L) lane L's
+// (L uniform).  Slots a fixed step apart take one lane read and a scalar addition.
+struct StepIndex {
+    int32_t base;
+    int step;
+    __device__ __forceinline__ int32_t operator()(int r) const { return base + r * step; }
+    __device__ __forceinline__ int32_t of(int r, int L) const { return lane_i32(base, L) + r * step; }
+};
+
+template <typename F>
+struct AnyIndex {
+    const F &f;
+    __device__ __forceinline__ int32_t operator()(int r) const { return f(r); }
+    __device__ __forceinline__ int32_t of(int r, int L) const { return lane_i32(f(r), L); }
+};
+
+template <typename F>
+__device__ __forceinline__ AnyIndex<F> any_index(const F &f)
+{
+    return AnyIndex<F>{f};
+}
+
 // Least (T, E, index) candidate among those with pred(r) true.  Fast path when exactly
 // one candidate of the wave qualifies; otherwise a full lexicographic reduction.
 template <int R, typename Index, typename Pred>
@@ -121,7 +143,7 @@ __device__ __forceinline__ Key chunk_pick(const double (&vT)[R], const double (&
             cnt += __popcll(m);
             const int L = __ffsll((long long)m) - 1;
             one = Key{lane_u64(dbits(vT[r]), L), lane_u64(dbits(vE[r]), L),
-                      lane_i32(index(r), L)};
+                      index.of(r, L)};
         }
     }
     if (cnt == 1) return one;
@@ -143,8 +165,7 @@ struct Scratch {
 };
 
 // Frontier of the wave's chunk (invalid slots hold T = E = +inf; valid ones are
-// finite); tl, el are each lane's least T and E.  index(r) is the candidate index of this
-// lane's slot r.  Writes the frontier in ascending T to o*[0 .. n) and returns n
+// finite); tl, el are each lane's least T and E; index as above.  Writes the frontier in ascending T to o*[0 .. n) and returns n
 // (uniform).
 //
 // A (least in (T, E, index) order) and Z (least in (E, T, index) order) come from wave
