@@ -198,7 +198,7 @@ __device__ __forceinline__ int rank_in(const double *bT, const double *bE, const
 // the merged frontier's size.  Every thread of the block must call.  beat() is called every
 // now and then (see finalize_fused_kernel).
 template <int NT, typename Beat>
-__device__ inline int merge_pair(const PointBufs &in, const PointBufs &out, uint8_t *flags,
+__device__ inline int merge_pair(PointBufs in, PointBufs out, uint8_t *flags,
                                  int64_t sa, int na, int64_t sb, int nb, const Beat &beat)
 {
     __shared__ int32_t sc[NT / 64];
@@ -564,6 +564,7 @@ __device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs
         total += tot;
     }
     if (small_units && threadIdx.x == 0) sh.upre[nu] = (int)total;
+    static_assert(NT <= KR_FIN_UNITS, "a prefix entry per thread");
     __syncthreads();
     if (small_units && total <= KR_FIN_CAP) {
         const int n = (int)total;
@@ -586,19 +587,31 @@ __device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs
         return cnt;
     }
     // Large union: gather contiguously into fin, reduce LDS-sized chunks in place,
-    // then merge the chunk staircases pairwise (fin <-> buf).
-    int64_t pre = 0;
-    for (int k = 0; k < nu; ++k) {
-        const int n = ld_l2(ucnt + u0 + k);
-        const int64_t src = s0 + (int64_t)k * L.unit_stride;
-        for (int x = threadIdx.x; x < n; x += NT) {
-            fin.T[s0 + pre + x] = buf.T[src + x];
-            fin.E[s0 + pre + x] = buf.E[src + x];
-            fin.I[s0 + pre + x] = buf.I[src + x];
+    // then merge the chunk staircases pairwise (fin <-> buf).  A wave takes a unit, or the
+    // block where the units have many points: the block took 1.5 us for a unit however few
+    // they were (512 frequencies of a microbatch, 20 configurations each: 773 us).
+    const int per = total < (int64_t)nu * (NT / 2) ? 64 : NT;  // threads to a unit
+    int64_t pre = s0;
+    for (int k0 = 0; k0 < nu; k0 += NT) {
+        const int k = k0 + threadIdx.x;
+        int tot;
+        const int ex = block_exclusive<int, SumI32, NT / 64>(k < nu ? ucnt[u0 + k] : 0, 0, SumI32(),
+                                                             sc, &tot);
+        sh.upre[threadIdx.x] = ex;
+        if (threadIdx.x == 0) sh.upre[NT] = tot;
+        __syncthreads();
+        for (int j = threadIdx.x / per; j < min(NT, nu - k0); j += NT / per) {
+            const int at = sh.upre[j], n = sh.upre[j + 1] - at;
+            const int64_t src = s0 + (int64_t)(k0 + j) * L.unit_stride, dst = pre + at;
+            for (int x = threadIdx.x % per; x < n; x += per) {
+                fin.T[dst + x] = buf.T[src + x];
+                fin.E[dst + x] = buf.E[src + x];
+                fin.I[dst + x] = buf.I[src + x];
+            }
         }
-        pre += n;
+        pre += tot;
+        __syncthreads();
     }
-    __syncthreads();
     int32_t *rc = runcnt + s0 / KR_FIN_CAP + g;
     const int nchunks = (int)((total + KR_FIN_CAP - 1) / KR_FIN_CAP);
     for (int c = 0; c < nchunks; ++c) {
@@ -701,8 +714,7 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
         __device__ Lds() {}
     };
     __shared__ Lds sh;
-    __shared__ int32_t s_seg, s_beats;
-    __shared__ int32_t *s_beat;
+    __shared__ int32_t s_seg;
     __shared__ int32_t sc32[NT / 64];
     __shared__ int64_t sc64[NT / 64];
     const int tid = threadIdx.x;
@@ -713,15 +725,10 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
         g = s_seg;
         if (g < 0 || g >= L.n_seg) return;  // another call's ticket
     }
-    // The beat's place and number wait in LDS: the kernel has no scalar register to spare (1 M
-    // points in one segment took 2.5 % longer with them there).
-    if (!RAW && tid == 0) {
-        s_beat = L.n_seg > 1 ? fcnt + g : nullptr;
-        s_beats = 0;
-    }
+    int32_t beats = 0;
     auto beat = [&] {
-        if (threadIdx.x == 0 && s_beat)
-            __hip_atomic_store(s_beat, --s_beats, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (L.n_seg > 1 && threadIdx.x == 0)
+            __hip_atomic_store(fcnt + g, --beats, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     // the first output element of segment g, which holds `count` points (cap: a wait was given
     // up).  A count given up makes the sum of up to KR_FUSED_SEGS counts negative.
