@@ -13,8 +13,8 @@
 // scanned: a 256-thread block per segment of up to 512 points, a 1024-thread block
 // for the few segments of up to 4096, and beyond that LDS-sized chunks whose
 // frontiers are merged pairwise in device memory; with up to KR_FUSED_SEGS segments one
-// launch does all of this and copies out (finalize_fused_kernel).  A pairwise merge of two staircases
-// needs no sort: an element's rank in the partner comes from a binary search, and it
+// launch does all of this and copies out (finalize_fused_kernel).  A pairwise merge of two
+// staircases needs no sort: an element's rank in the partner comes from a binary search, and it
 // survives iff the partner element just before it in key order has a larger E.
 #include "kr_filter.h"
 #include "kr_launch.h"
@@ -265,9 +265,8 @@ struct FinLds {
 // Segments of at most NT * PER points in at most NT units: one block of NT threads
 // per segment sorts the union in LDS by merging.  Thread t gathers points t * PER ..
 // t * PER + PER - 1 and sorts them in registers; the sorted runs are then merged
-// pairwise, one level per doubling of the run width.  At a level every point finds
-// its rank in the partner run by a binary search and moves to (its place in its own
-// run) + (that rank) -- keys are distinct, so the places form a permutation.  The
+// pairwise, one level per doubling of the run width, every thread forming PER outputs of a
+// level (merge path: a search for where they start, then a merge in registers).  The
 // levels move (T, 16-bit point id) pairs between two buffers; E and the index stay in
 // place and are read on a tie in T only.  A strict prefix-minimum scan of E over the
 // sorted order gives the frontier.
@@ -541,55 +540,31 @@ finalize_large_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs
     }
 }
 
-// Stage 3, the segments on the second list: one block per segment (blocks loop over
-// the list), returning the frontier's size.  The union is sorted in LDS when it fits; otherwise it is cut into
-// LDS-sized chunks whose frontiers are merged pairwise in device memory.
-template <int NT, typename Beat>
-__device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs &buf,
-                                      const int32_t *ucnt, const PointBufs &fin, int32_t *runcnt,
-                                      uint8_t *flags, FinLds &sh, int32_t *sc, const Beat &beat)
+// Stage 3, the segments on the second list: one block per segment (blocks loop over the list).
+// The union is sorted in LDS when it fits; otherwise it is cut into LDS-sized chunks whose
+// frontiers are merged pairwise in device memory.
+
+// A segment's union in chunks; returns the frontier's size.  upre: NT + 1 entries; cap: points
+// per chunk, at least KR_FIN_CAP; chunk(x, n) replaces the n points at element x of `fin` by
+// their frontier and returns its size, in every thread.
+template <int NT, typename Beat, typename Chunk>
+__device__ __forceinline__ int finalize_chunks(int g, const SegLayout &L, const PointBufs &buf,
+                                               const int32_t *ucnt, const PointBufs &fin,
+                                               int32_t *runcnt, uint8_t *flags, int32_t *upre,
+                                               int32_t *sc, int cap, const Beat &beat,
+                                               const Chunk &chunk)
 {
     const int64_t s0 = L.seg_off[g];
     const int64_t u0 = L.unit_base[g];
     const int nu = (int)(L.unit_base[g + 1] - u0);
-    // unit sizes and their running offsets
     int64_t total = 0;
-    const bool small_units = nu <= KR_FIN_UNITS;
     for (int c0 = 0; c0 < nu; c0 += NT) {
         const int k = c0 + threadIdx.x;
-        const int n = k < nu ? ucnt[u0 + k] : 0;
-        int tot;
-        const int ex = block_exclusive<int, SumI32, NT / 64>(n, 0, SumI32(), sc, &tot);
-        if (small_units && k < nu) sh.upre[k] = (int)total + ex;
-        total += tot;
+        total += block_reduce<int, SumI32, NT / 64>(k < nu ? ucnt[u0 + k] : 0, 0, SumI32(), sc);
     }
-    if (small_units && threadIdx.x == 0) sh.upre[nu] = (int)total;
-    static_assert(NT <= KR_FIN_UNITS, "a prefix entry per thread");
-    __syncthreads();
-    if (small_units && total <= KR_FIN_CAP) {
-        const int n = (int)total;
-        for (int x = threadIdx.x; x < n; x += NT) {
-            int lo = 0, hi = nu - 1;  // unit holding element x
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (sh.upre[mid] <= x) lo = mid;
-                else hi = mid - 1;
-            }
-            const int64_t src = s0 + (int64_t)lo * L.unit_stride + (x - sh.upre[lo]);
-            sh.sT[x] = dbits(buf.T[src]);
-            sh.sE[x] = dbits(buf.E[src]);
-            sh.sI[x] = buf.I[src];
-        }
-        __syncthreads();
-        lds_sort_keys<NT>(sh.sT, sh.sE, sh.sI, n);
-        const int cnt = lds_frontier_scan<NT>(sh.sT, sh.sE, sh.sI, n, fin.T + s0, fin.E + s0,
-                                              fin.I + s0);
-        return cnt;
-    }
-    // Large union: gather contiguously into fin, reduce LDS-sized chunks in place,
-    // then merge the chunk staircases pairwise (fin <-> buf).  A wave takes a unit, or the
-    // block where the units have many points: the block took 1.5 us for a unit however few
-    // they were (512 frequencies of a microbatch, 20 configurations each: 773 us).
+    // Gather contiguously into fin.  A wave takes a unit, or the block where the units have
+    // many points: the block took 1.5 us for a unit however few they were (512 frequencies of
+    // a microbatch, 20 configurations each: 773 us).
     const int per = total < (int64_t)nu * (NT / 2) ? 64 : NT;  // threads to a unit
     int64_t pre = s0;
     for (int k0 = 0; k0 < nu; k0 += NT) {
@@ -597,11 +572,11 @@ __device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs
         int tot;
         const int ex = block_exclusive<int, SumI32, NT / 64>(k < nu ? ucnt[u0 + k] : 0, 0, SumI32(),
                                                              sc, &tot);
-        sh.upre[threadIdx.x] = ex;
-        if (threadIdx.x == 0) sh.upre[NT] = tot;
+        upre[threadIdx.x] = ex;
+        if (threadIdx.x == 0) upre[NT] = tot;
         __syncthreads();
         for (int j = threadIdx.x / per; j < min(NT, nu - k0); j += NT / per) {
-            const int at = sh.upre[j], n = sh.upre[j + 1] - at;
+            const int at = upre[j], n = upre[j + 1] - at;
             const int64_t src = s0 + (int64_t)(k0 + j) * L.unit_stride, dst = pre + at;
             for (int x = threadIdx.x % per; x < n; x += per) {
                 fin.T[dst + x] = buf.T[src + x];
@@ -612,32 +587,24 @@ __device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs
         pre += tot;
         __syncthreads();
     }
+    // reduce the chunks in place, then merge their staircases pairwise (fin <-> buf)
     int32_t *rc = runcnt + s0 / KR_FIN_CAP + g;
-    const int nchunks = (int)((total + KR_FIN_CAP - 1) / KR_FIN_CAP);
+    const int nchunks = (int)((total + cap - 1) / cap);
     for (int c = 0; c < nchunks; ++c) {
         beat();
-        const int64_t c0 = (int64_t)c * KR_FIN_CAP;
-        const int n = (int)min((int64_t)KR_FIN_CAP, total - c0);
-        for (int x = threadIdx.x; x < n; x += NT) {
-            sh.sT[x] = dbits(ld_l2(fin.T + s0 + c0 + x));
-            sh.sE[x] = dbits(ld_l2(fin.E + s0 + c0 + x));
-            sh.sI[x] = ld_l2(fin.I + s0 + c0 + x);
-        }
-        __syncthreads();
-        lds_sort_keys<NT>(sh.sT, sh.sE, sh.sI, n);
-        const int cnt = lds_frontier_scan<NT>(sh.sT, sh.sE, sh.sI, n, fin.T + s0 + c0, fin.E + s0 + c0,
-                                          fin.I + s0 + c0);
+        const int64_t c0 = (int64_t)c * cap;
+        const int cnt = chunk(s0 + c0, (int)min((int64_t)cap, total - c0));
         if (threadIdx.x == 0) rc[c] = cnt;
         __syncthreads();
     }
     PointBufs cur = fin, other = buf;
     for (int span = 1; span < nchunks; span <<= 1) {
         for (int r = 0; r < nchunks; r += 2 * span) {
-            const int64_t sa = s0 + (int64_t)r * KR_FIN_CAP;
+            const int64_t sa = s0 + (int64_t)r * cap;
             const int na = ld_l2(rc + r);
             int merged;
             if (r + span < nchunks) {
-                const int64_t sb = s0 + (int64_t)(r + span) * KR_FIN_CAP;
+                const int64_t sb = s0 + (int64_t)(r + span) * cap;
                 merged = merge_pair<NT>(cur, other, flags, sa, na, sb, ld_l2(rc + r + span),
                                         beat);
             } else {
@@ -667,6 +634,43 @@ __device__ int finalize_block_segment(int g, const SegLayout &L, const PointBufs
     return n;
 }
 
+// A union of up to KR_FIN_CAP points in up to KR_FIN_UNITS units; -1 if it is larger.
+__device__ __forceinline__ int finalize_few(int g, const SegLayout &L, const PointBufs &buf,
+                                            const int32_t *ucnt, const PointBufs &fin, FinLds &sh,
+                                            int32_t *sc)
+{
+    const int64_t s0 = L.seg_off[g];
+    const int64_t u0 = L.unit_base[g];
+    const int nu = (int)(L.unit_base[g + 1] - u0);
+    if (nu > KR_FIN_UNITS) return -1;
+    int64_t total = 0;
+    for (int c0 = 0; c0 < nu; c0 += KR_BLOCK) {
+        const int k = c0 + threadIdx.x;
+        int tot;
+        const int ex = block_exclusive(k < nu ? ucnt[u0 + k] : 0, 0, SumI32(), sc, &tot);
+        if (k < nu) sh.upre[k] = (int)total + ex;
+        total += tot;
+    }
+    __syncthreads();
+    if (total > KR_FIN_CAP) return -1;
+    const int n = (int)total;
+    for (int x = threadIdx.x; x < n; x += KR_BLOCK) {
+        int lo = 0, hi = nu - 1;  // unit holding element x
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (sh.upre[mid] <= x) lo = mid;
+            else hi = mid - 1;
+        }
+        const int64_t src = s0 + (int64_t)lo * L.unit_stride + (x - sh.upre[lo]);
+        sh.sT[x] = dbits(buf.T[src]);
+        sh.sE[x] = dbits(buf.E[src]);
+        sh.sI[x] = buf.I[src];
+    }
+    __syncthreads();
+    lds_sort_keys(sh.sT, sh.sE, sh.sI, n);
+    return lds_frontier_scan(sh.sT, sh.sE, sh.sI, n, fin.T + s0, fin.E + s0, fin.I + s0);
+}
+
 __global__ void __launch_bounds__(KR_BLOCK)
 finalize_block_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs fin,
                       int32_t *fcnt, int32_t *runcnt, uint8_t *flags, const int32_t *lists)
@@ -676,8 +680,23 @@ finalize_block_kernel(SegLayout L, PointBufs buf, const int32_t *ucnt, PointBufs
     const int cnt = lists[1];
     for (int i = blockIdx.x; i < cnt; i += gridDim.x) {
         const int g = lists[2 + L.n_seg + i];
-        const int n = finalize_block_segment<KR_BLOCK>(g, L, buf, ucnt, fin, runcnt, flags, sh, sc,
-                                                       [] {});
+        int n = finalize_few(g, L, buf, ucnt, fin, sh, sc);
+        if (n < 0) {
+            __syncthreads();
+            auto chunk = [&](int64_t x0, int m) {
+                for (int x = threadIdx.x; x < m; x += KR_BLOCK) {
+                    sh.sT[x] = dbits(ld_l2(fin.T + x0 + x));
+                    sh.sE[x] = dbits(ld_l2(fin.E + x0 + x));
+                    sh.sI[x] = ld_l2(fin.I + x0 + x);
+                }
+                __syncthreads();
+                lds_sort_keys(sh.sT, sh.sE, sh.sI, m);
+                return lds_frontier_scan(sh.sT, sh.sE, sh.sI, m, fin.T + x0, fin.E + x0,
+                                         fin.I + x0);
+            };
+            n = finalize_chunks<KR_BLOCK>(g, L, buf, ucnt, fin, runcnt, flags, sh.upre, sc,
+                                          KR_FIN_CAP, [] {}, chunk);
+        }
         if (threadIdx.x == 0) fcnt[g] = n;
         __syncthreads();  // LDS reuse by the next segment
     }
@@ -710,7 +729,7 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
     constexpr int NT = KR_FM_LARGE_NT, PER = KR_FM_LARGE_PER;
     union Lds {
         MergeLds<NT, PER> merge;
-        FinLds fin;
+        int32_t upre[NT + 1];
         __device__ Lds() {}
     };
     __shared__ Lds sh;
@@ -800,7 +819,26 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
         return;
     }
     __syncthreads();
-    n = finalize_block_segment<NT>(g, L, buf, ucnt, fin, runcnt, flags, sh.fin, sc32, beat);
+    // Chunks of the merge sort's capacity, sorted by it: a union of about 5,000 points 87 us, with
+    // bitonic chunks of 2,560 198 us (and with tile frontiers in front 135).
+    auto chunk = [&](int64_t x0, int m) {
+        auto points = [&](int q0, int q1, MKey (&k)[PER]) {
+#pragma unroll
+            for (int j = 0; j < PER; ++j)
+                if (q0 + j < q1) {
+                    const int64_t x = x0 + q0 + j;
+                    k[j] = MKey{dbits(ld_l2(fin.T + x)), dbits(ld_l2(fin.E + x)), ld_l2(fin.I + x)};
+                }
+        };
+        int kept = 0;
+        merge_segment(m, points, sh.merge, fin.T, fin.E, fin.I, INT64_MAX, [&](int count) {
+            kept = count;
+            return x0;
+        });
+        return kept;
+    };
+    n = finalize_chunks<NT>(g, L, buf, ucnt, fin, runcnt, flags, sh.upre, sc32, kFusedCap, beat,
+                            chunk);
     __syncthreads();  // the block's stores to fin are read back below
     const int64_t d0 = place(n), src0 = L.seg_off[g];
     for (int64_t x = tid; x < n && d0 + x < o.cap; x += NT) {
