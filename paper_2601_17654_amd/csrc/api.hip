@@ -113,7 +113,7 @@ bool wave_plan(EvalArgs *a)
     return true;
 }
 
-// Two comm kernels and at most 8 SM choices: one wave per slab, lane (s1, s2).
+// Two comm kernels and at most 8 SM choices: KR_PAIR_WAVES waves per slab, lane (s1, s2).
 bool pair_plan(EvalArgs *a)
 {
     if (a->M != 2 || a->S > 8) return false;
@@ -129,8 +129,8 @@ bool pair_plan(EvalArgs *a)
     // scratch T, E, indices per wave; room for two 16-bit champions per position before that
     a->q_l = a->q_sc + (int)std::max<int64_t>(NW * (64 + 64 + 32), (a->n_pos + 1) / 2);
     const int64_t lds = a->q_l + 2 * a->S + (2 * pairs + 3) / 4;
-    // slabs of the sums and the fresh table that leave 17 KB of the budget; the largest of
-    // them ask for up to 70 KB in all
+    // slabs whose sums and fresh table leave 17 KB of the budget; in all they ask for up to
+    // 64,656 bytes (7 SM choices, 81 kernels, 81 positions)
     if ((size_t)(a->q_c + NW * (6 * 64 + 160)) * 8 > kLdsBudget) return false;
     a->pair = 1;
     a->lds_doubles = (int)lds;

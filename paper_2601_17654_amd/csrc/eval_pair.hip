@@ -35,8 +35,8 @@
 // Of what is evaluated, most is beaten in time and energy by the wave's best candidate of the
 // slab so far (least E + mean power T); the rest gathers in the wave's scratch, 64 candidates to
 // a frontier, instead of taking a frontier per launch position (with the end of the first comm
-// phase tabled and a slab's frontiers merged one point per lane: 373 -> 268 us).  What is left
-// is latency: of those 268 us the sums, the table and the pruning take about 65, the
+// phase tabled and a slab's frontiers merged one point per lane: 373 -> 268 us, up to 287 on
+// other boxes).  What is left is latency: of those 268 us the sums, the table and the pruning take about 65, the
 // positions' phases about 100.
 // A phase is kept as the values it adds to the energy sum and to the time, in the
 // order the walk adds them.  A candidate applies them to its own sums in that order,
@@ -296,8 +296,8 @@ __device__ __forceinline__ void wave_max2_f64(double &x, double &y)
 // replaced in place by their frontier: up to 64 one per lane, more by a sort in the
 // second-phase tables, idle by then, when they fit there.  SC > 0 fixes the number of
 // SM choices at compile time (four blocks share a compute unit then, by registers and LDS:
-// 370 us against 444 us with three, before candidates were gathered); FN also fixes the two-comm workload's 48 kernels and 33
-// launch positions.
+// 370 us against 444 us with three, before candidates were gathered); FN also fixes the
+// two-comm workload's 48 kernels and 33 launch positions.
 template <int R, int W, int NW, int SC, bool FN>
 __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kernel(EvalArgs a, UnitOut o)
 {
@@ -331,8 +331,8 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
     int16_t *const list = (int16_t *)(lds + a.q_l + 2 * S);  // [np * S]
     const int npS = np * S;
     int16_t *const first = list + npS;  // [np * S]: where the first comm phase ends
-    // sort room of the slab-end reduction: this wave's share of the fresh and continuing
-    // tables
+    // sort room of the slab-end reduction: this wave's share of the fresh table and the pairs'
+    // own parts
     const int scap = a.pair_scap;
     uint64_t *const sT = (uint64_t *)(lds + a.q_f) + (size_t)wave * ((a.q_sc - a.q_f) / NW);
     uint64_t *const sE = sT + scap;
@@ -701,6 +701,8 @@ __global__ void __launch_bounds__(64 * NW, SC > 0 ? 4 : 3) eval_filter_pair_kern
 
 int pair_owner_host(int p1, int NW) { return pair_owner(p1, NW); }
 
+// Instances: 8 SM choices at compile time (30 kernels, 31 positions: 84 us, general 106), and the
+// two-comm workload's sizes (287 us, 303 with the SM choices alone, 391 general).
 hipError_t launch_eval_filter_pair(const EvalArgs &a, const UnitOut &o, hipStream_t st)
 {
     const size_t lds = (size_t)a.lds_doubles * sizeof(double);

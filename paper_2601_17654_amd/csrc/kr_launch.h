@@ -52,9 +52,9 @@ struct EvalArgs {
     // for it takes the sizes, the LDS layout and the validity of all but the last round
     // as compile-time facts
     int fixed32;
-    // one wave per slab (two comm kernels, at most 8 SM choices): LDS offsets (doubles)
-    // of the power slab, the running sums, the fresh and continuing second-phase
-    // records, the filter scratch and the list of second-phase pairs kept
+    // four waves per slab (two comm kernels, at most 8 SM choices): LDS offsets (doubles)
+    // of the power slab, the running sums, the fresh second-phase records, the pairs' own
+    // parts, the filter scratch and the list of second-phase pairs kept
     int pair;
     int q_pw, q_ab, q_f, q_c, q_sc, q_l;
     int pair_scap;          // most chunk outputs of a slab a wave reduces to its frontier on chip

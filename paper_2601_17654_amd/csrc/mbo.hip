@@ -14,7 +14,7 @@
 // Selection.  Every pass is a top-k by (score descending, index ascending) over the
 // partition's unmeasured candidates, with k <= 64.  A wave keeps its best entries sorted
 // across its lanes; new candidates are compared against the k-th of them, and those that
-// beat it are collected, sorted (bitonic, lane shuffles) and merged in (reverse, lane-wise
+// beat it are collected, sorted (by counting better ones) and merged in (reverse, lane-wise
 // better, bitonic merge) 64 at a time.  Tiles of a partition reduce to one sorted list per
 // pass; one block per partition merges the tile lists and assembles the batch in pass order.
 #include <math.h>

@@ -40,3 +40,24 @@ def test_many_partitions_match_the_oracle(oracle_lib, shape):
         s = slice(off[p], off[p + 1])
         assert np.array_equal(idx[s], ix), p
         assert np.array_equal(T[s], rT) and np.array_equal(E[s], rE), p
+
+
+@pytest.mark.parametrize("n_seg", [1, 260], ids=["one launch", "stages"])
+@pytest.mark.parametrize("n", [2_200_000, 4_400_000])
+@pytest.mark.parametrize("how", ["few", "some"])
+def test_many_units(oracle_lib, n, how, n_seg):
+    """A segment of more units than a block has threads, or than its LDS has room for: a point
+    or two of each, and a few of each (more than a merge in LDS takes)."""
+    import torch
+
+    from paper_2601_17654_amd import binding as kr
+
+    rng = np.random.default_rng(n)
+    T = rng.uniform(1.0, 2.0, n)
+    E = T + rng.uniform(0.0, 1e-6, n) if how == "few" else rng.uniform(1.0, 2.0, n)
+    off = np.concatenate([[0], np.full(n_seg - 1, 5), [n - 5 * (n_seg - 1)]]).cumsum()
+    fr = kr.pareto_filter(torch.from_numpy(T).cuda(), torch.from_numpy(E).cuda(), off)
+    o, idx = fr.off.cpu().numpy(), fr.idx.cpu().numpy()
+    for g in range(n_seg):
+        s = slice(off[g], off[g + 1])
+        assert np.array_equal(idx[o[g]:o[g + 1]], oracle_lib.pareto(T[s], E[s])), g
