@@ -330,10 +330,11 @@ __device__ __forceinline__ bool merge_prefix(int g, const SegLayout &L, const in
     return true;
 }
 
-// The points of a segment's units (after merge_prefix): load(q, key) for q in [q0, q1).
-template <int NT, int PER>
+// The points of a segment's up to NU units (upre as merge_prefix leaves it): load(q, key) for q
+// in [q0, q1).
+template <int NU, int PER>
 struct UnitPoints {
-    const MergeLds<NT, PER> &sh;
+    const int32_t *upre;
     const PointBufs &buf;
     int64_t s0, stride;
     int nu;
@@ -342,14 +343,14 @@ struct UnitPoints {
     {
         int u = 0;  // unit holding point q0: the last u < nu with upre[u] <= q0
 #pragma unroll
-        for (int step = NT / 2; step >= 1; step >>= 1)
-            if (u + step < nu && sh.upre[u + step] <= q0) u += step;
+        for (int step = NU / 2; step >= 1; step >>= 1)
+            if (u + step < nu && upre[u + step] <= q0) u += step;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int x = q0 + j;
             if (x < q1) {
-                while (sh.upre[u + 1] <= x) ++u;  // skip ended and empty units (x < upre[nu])
-                const int64_t src = s0 + (int64_t)u * stride + (x - sh.upre[u]);
+                while (upre[u + 1] <= x) ++u;  // skip ended and empty units (x < upre[nu])
+                const int64_t src = s0 + (int64_t)u * stride + (x - upre[u]);
                 k[j] = MKey{dbits(buf.T[src]), dbits(buf.E[src]), buf.I[src]};
             }
         }
@@ -489,7 +490,7 @@ __device__ __forceinline__ void merge_units(int g, int n, const SegLayout &L, co
                                             MergeLds<NT, PER> &sh)
 {
     const int64_t s0 = L.seg_off[g];
-    const UnitPoints<NT, PER> points{sh, buf, s0, L.unit_stride,
+    const UnitPoints<NT, PER> points{sh.upre, buf, s0, L.unit_stride,
                                      (int)(L.unit_base[g + 1] - L.unit_base[g])};
     merge_segment(n, points, sh, fin.T, fin.E, fin.I, INT64_MAX, [&](int count) {
         if (threadIdx.x == 0) fcnt[g] = count;
@@ -729,13 +730,15 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
     constexpr int NT = KR_FM_LARGE_NT, PER = KR_FM_LARGE_PER;
     union Lds {
         MergeLds<NT, PER> merge;
+        MergeLds<KR_FM_SMALL_NT, KR_FM_SMALL_PER> small;  // below merge.upre
         int32_t upre[NT + 1];
         __device__ Lds() {}
     };
     __shared__ Lds sh;
     __shared__ int32_t s_seg;
     __shared__ int32_t sc32[NT / 64];
-    __shared__ int64_t sc64[NT / 64];
+    __shared__ int64_t sc64[NT / 64], sc_small[KR_FM_SMALL_NT / 64];
+    static_assert(sizeof(sh.small) <= 32 * NT * PER, "the prefix stays clear of it");
     const int tid = threadIdx.x;
     int g = 0;
     if (L.n_seg > 1) {
@@ -752,10 +755,11 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
     // the first output element of segment g, which holds `count` points (cap: a wait was given
     // up).  A count given up makes the sum of up to KR_FUSED_SEGS counts negative.
     constexpr int64_t kLost = -((int64_t)1 << 50);
-    auto place = [&](int count) -> int64_t {
+    auto place = [&](int count, auto &sc) -> int64_t {  // sc: a word per wave of the block
         int64_t d0 = 0;
         if (L.n_seg > 1) {
-            static_assert(KR_FUSED_SEGS <= NT, "a thread per earlier segment");
+            static_assert(KR_FUSED_SEGS <= KR_FM_SMALL_NT, "a thread per earlier segment");
+            constexpr int NW = sizeof(sc) / sizeof(sc[0]);
             if (tid == 0)
                 __hip_atomic_store(fcnt + g, count + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             int64_t before = 0;
@@ -769,7 +773,7 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
                 }
                 before = c > 0 ? c - 1 : kLost;
             }
-            d0 = block_reduce<int64_t, SumI64, NT / 64>(before, (int64_t)0, SumI64(), sc64);
+            d0 = block_reduce<int64_t, SumI64, NW>(before, (int64_t)0, SumI64(), sc);
             if (d0 < 0) {
                 if (tid == 0) {
                     if (o.status) __hip_atomic_store(o.status, (int32_t)KR_EHIP, __ATOMIC_RELAXED,
@@ -800,7 +804,8 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
                     k[j] = MKey{dbits(t), dbits(e), q0 + j};
                 }
         };
-        merge_segment(n, points, sh.merge, o.T, o.E, o.idx, o.cap, place);
+        merge_segment(n, points, sh.merge, o.T, o.E, o.idx, o.cap,
+                      [&](int count) { return place(count, sc64); });
         if (o.status) {
             if (L.n_seg > 1) {
                 report_values(o.status, worst >= KR_BAD_HI);  // KR_OK before the launch
@@ -813,9 +818,22 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
     }
     int n;
     if (merge_prefix(g, L, ucnt, sh.merge, n)) {
-        const UnitPoints<NT, PER> points{sh.merge, buf, L.seg_off[g], L.unit_stride,
-                                         (int)(L.unit_base[g + 1] - L.unit_base[g])};
-        merge_segment(n, points, sh.merge, o.T, o.E, o.idx, o.cap, place);
+        const int nu = (int)(L.unit_base[g + 1] - L.unit_base[g]);
+        __syncthreads();  // upre
+        if (n <= KR_FM_SMALL_NT * KR_FM_SMALL_PER) {
+            // Few points: four waves, the others end (a barrier waits for no ended wave).  256
+            // segments of 100 points took 120 us a call with all sixteen, 115 so, and 112 with
+            // launches of their own.
+            if (tid >= KR_FM_SMALL_NT) return;
+            const UnitPoints<NT, KR_FM_SMALL_PER> points{sh.merge.upre, buf, L.seg_off[g],
+                                                         L.unit_stride, nu};
+            merge_segment(n, points, sh.small, o.T, o.E, o.idx, o.cap,
+                          [&](int count) { return place(count, sc_small); });
+            return;
+        }
+        const UnitPoints<NT, PER> points{sh.merge.upre, buf, L.seg_off[g], L.unit_stride, nu};
+        merge_segment(n, points, sh.merge, o.T, o.E, o.idx, o.cap,
+                      [&](int count) { return place(count, sc64); });
         return;
     }
     __syncthreads();
@@ -840,7 +858,7 @@ finalize_fused_kernel(const double *T, const double *E, int64_t n_total, SegLayo
     n = finalize_chunks<NT>(g, L, buf, ucnt, fin, runcnt, flags, sh.upre, sc32, kFusedCap, beat,
                             chunk);
     __syncthreads();  // the block's stores to fin are read back below
-    const int64_t d0 = place(n), src0 = L.seg_off[g];
+    const int64_t d0 = place(n, sc64), src0 = L.seg_off[g];
     for (int64_t x = tid; x < n && d0 + x < o.cap; x += NT) {
         o.idx[d0 + x] = ld_l2(fin.I + src0 + x);
         o.T[d0 + x] = ld_l2(fin.T + src0 + x);
