@@ -134,6 +134,14 @@ __device__ __forceinline__ int dp_decode(const DpArgs &a, int i, int j, int r, i
     return 96 + r + 1;
 }
 
+// Whether a walk back goes on from cell (i, j).  Kept points are strictly ordered in time
+// unless a time is not a number; then a place behind the others stays unwritten and the
+// back-pointer read there may be anything, so the walk ends outside the table as well.
+__device__ __forceinline__ bool dp_inside(const DpArgs &a, int i, int j)
+{
+    return i <= a.I && j <= a.J && !(i == a.I && j == a.J);
+}
+
 // Byte offsets of the LDS sections of one instance (all 8-byte aligned).
 struct DpLds {
     int ops, arT, arE, cT, cE, sT, sE, soff, sstart, arB, cstart, ccnt, csrc, keep, bytes;
@@ -359,13 +367,13 @@ __device__ bool dp_solve(const DpArgs &a, int64_t inst, char *lds, int arena, in
         if (a.out_sched) {
             int32_t *sc = a.out_sched + o * nops;
             int ci = 0, cj = 0, cq = q, d = 0;
-            while (!(ci == a.I && cj == a.J) && d < nops) {
-                const int b = arB[cstart[ci * W + cj] + cq];
+            while (dp_inside(a, ci, cj) && d < nops) {
+                const int b = arB[min(cstart[ci * W + cj] + cq, arena - 1)];
                 int ni, nj;
-                sc[d++] = dp_decode(a, ci, cj, b / 64, &ni, &nj);
+                sc[d++] = dp_decode(a, ci, cj, b >> 6, &ni, &nj);
                 ci = ni;
                 cj = nj;
-                cq = b % 64;
+                cq = b & 63;
             }
             for (; d < nops; ++d) sc[d] = -1;
         }
@@ -672,13 +680,13 @@ __device__ __forceinline__ void dp_quad(const DpArgs &a, int64_t grp, int64_t n,
         if (a.out_sched) {
             int32_t *sc = a.out_sched + o * nops;
             int ci = 0, cj = 0, cq = p, d = 0;
-            while (!(ci == a.I && cj == a.J) && d < nops) {
-                const int b = arB[(cell[ci * W + cj] >> 8) + cq];
+            while (dp_inside(a, ci, cj) && d < nops) {
+                const int b = arB[min((cell[ci * W + cj] >> 8) + cq, pool - 1)];
                 int ni, nj;
-                sc[d++] = dp_decode(a, ci, cj, b / 64, &ni, &nj);
+                sc[d++] = dp_decode(a, ci, cj, b >> 6, &ni, &nj);
                 ci = ni;
                 cj = nj;
-                cq = b % 64;
+                cq = b & 63;
             }
             for (; d < nops; ++d) sc[d] = -1;
         }
