@@ -153,7 +153,10 @@ bool pair_plan(EvalArgs *a)
     int64_t share[NW] = {};
     for (int p1 = 0; p1 < a->n_pos; ++p1) share[pair_owner_host(p1, NW)] += a->n_pos - p1;
     a->uper = NW * (int64_t)a->nfb;
-    a->ustride = (int64_t)a->fb * *std::max_element(share, share + NW) * a->S * a->S;
+    // a wave's candidates of a slab, and a point more for each frontier of one candidate
+    // (wave_frontier): two frontiers in a row are of more than 64 together
+    const int64_t cands = *std::max_element(share, share + NW) * a->S * a->S;
+    a->ustride = a->fb * (cands + cands / 32 + 2);
     a->useg = a->uper * a->ustride;
     return true;
 }

@@ -338,8 +338,9 @@ __global__ void __launch_bounds__(64, OCC) eval_filter_wave_kernel(EvalArgs a, U
                 tc_next = a.tc[pn * S + s];
                 pc_next = a.pc[pn * S + s];
             }
-            count += wave_frontier<R>(vT, vE, tl, el, StepIndex{f * a.Cf + c0 * S + s, S}, sc,
-                                      oT + count, oE + count, oI + count);
+            // with two SM choices or more a chunk has two candidates or more
+            count += wave_frontier<R, SC == 0>(vT, vE, tl, el, StepIndex{f * a.Cf + c0 * S + s, S},
+                                               sc, oT + count, oE + count, oI + count);
         }
     }
     if (lane == 0) o.cnt[blockIdx.x] = count;

@@ -165,8 +165,12 @@ struct Scratch {
 };
 
 // Frontier of the wave's chunk (invalid slots hold T = E = +inf; valid ones are
-// finite); tl, el are each lane's least T and E; index as above.  Writes the frontier in ascending T to o*[0 .. n) and returns n
-// (uniform).
+// finite); tl, el are each lane's least T and E; index as above.  Writes the frontier in
+// ascending T to o*[0 .. n) and returns n (uniform), at most the number of valid slots, or 2.
+// (Where no energy is a number below infinity, as unchecked tables can have it, the least one
+// is an empty slot's.)  LONE: at most the number of valid slots in any case, for callers whose
+// chunks may have one only and that have no room for another point; the test took 2 % of the
+// kernel on 138 M candidates.
 //
 // A (least in (T, E, index) order) and Z (least in (E, T, index) order) come from wave
 // minima and ballots over the slots.  Every other kept point lies strictly inside their box
@@ -174,7 +178,7 @@ struct Scratch {
 // gathered one candidate per lane and each keeps itself iff no other member precedes
 // it with energy at or below its own; kept points are placed by their rank in T.  A
 // box larger than the scratch takes repeated wave minima instead (same result).
-template <int R, typename Index>
+template <int R, bool LONE = false, typename Index>
 __device__ inline int wave_frontier(const double (&vT)[R], const double (&vE)[R], double tl,
                                     double el, const Index &index, const Scratch &sc, double *oT,
                                     double *oE, int32_t *oI)
@@ -186,7 +190,8 @@ __device__ inline int wave_frontier(const double (&vT)[R], const double (&vE)[R]
     const Key A = chunk_pick<R>(vT, vE, index, [&](int r) { return dbits(vT[r]) == tab; });
     const double TA = bitsd(A.t), EA = bitsd(A.e), EZ = el;
     const int32_t iA = A.i;
-    const bool single = A.e == ezb;  // A has the least energy too: A is Z, nothing beats it
+    // A has the least energy too: A is Z, nothing beats it
+    const bool single = A.e == ezb || (LONE && ezb >= KR_INF_BITS);
     int nkeep = 0;                   // kept points strictly inside the box
     if (!single) {
         const Key Z = chunk_pick<R>(vT, vE, index, [&](int r) { return dbits(vE[r]) == ezb; });
